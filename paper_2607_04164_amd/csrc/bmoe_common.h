@@ -235,6 +235,8 @@ hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part = 0);
 // segment on average); launch_ffn takes it when ffn_skinny_fits
 bool ffn_skinny_fits(const FfnArgs& a);
 hipError_t launch_ffn_skinny(const FfnArgs& a, hipStream_t s, int part);
+// fp32 layers (any shape)
+hipError_t launch_ffn_f32(const FfnArgs& a, hipStream_t s, int part);
 
 struct CombineArgs {
     const int32_t* slot_row;

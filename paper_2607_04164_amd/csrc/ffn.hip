@@ -18,7 +18,7 @@
 // M-tiles that share a weight panel run together on one XCD, and workgroups
 // past the real tile count exit at once.
 //
-// f32 path (small correctness configurations): one output element per thread.
+// fp32 layers: ffn_f32.hip.
 #include <cstdlib>
 #include <type_traits>
 
@@ -1190,57 +1190,6 @@ hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipS
     return hipGetLastError();
 }
 
-// ---- f32 path
-
-__device__ __forceinline__ int find_segment(const int32_t* offsets, int n_seg, int rows_cap, int row) {
-    for (int q = 0; q < n_seg; ++q) {
-        const int b = min(max(offsets[q], 0), rows_cap);
-        const int e = min(max(offsets[q + 1], b), rows_cap);
-        if (row >= b && row < e) return q;
-    }
-    return -1;
-}
-
-__global__ __launch_bounds__(256) void ffn_f32_gateup_kernel(const float* __restrict__ a,
-                                                             const float* __restrict__ wg,
-                                                             const float* __restrict__ wu,
-                                                             float* __restrict__ h,
-                                                             const int32_t* __restrict__ offsets,
-                                                             int n_seg, int rows_cap, int d, int d_ff,
-                                                             const int32_t* __restrict__ a_rows, int a_count) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)rows_cap * d_ff) return;
-    const int row = (int)(idx / d_ff), j = (int)(idx % d_ff);
-    const int s = find_segment(offsets, n_seg, rows_cap, row);
-    if (s < 0) return;
-    const float* ar = a + (size_t)gathered_row(a_rows, a_count, row) * d;
-    const float* gr = wg + ((size_t)s * d_ff + j) * d;
-    const float* ur = wu + ((size_t)s * d_ff + j) * d;
-    float g = 0.f, u = 0.f;
-    for (int c = 0; c < d; ++c) {
-        g = fmaf(ar[c], gr[c], g);
-        u = fmaf(ar[c], ur[c], u);
-    }
-    h[(size_t)row * d_ff + j] = g / (1.f + expf(-g)) * u;
-}
-
-__global__ __launch_bounds__(256) void ffn_f32_down_kernel(const float* __restrict__ h,
-                                                           const float* __restrict__ wd,
-                                                           float* __restrict__ y,
-                                                           const int32_t* __restrict__ offsets,
-                                                           int n_seg, int rows_cap, int d, int d_ff) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)rows_cap * d) return;
-    const int row = (int)(idx / d), i = (int)(idx % d);
-    const int s = find_segment(offsets, n_seg, rows_cap, row);
-    if (s < 0) return;
-    const float* hr = h + (size_t)row * d_ff;
-    const float* dr = wd + ((size_t)s * d + i) * d_ff;
-    float acc = 0.f;
-    for (int j = 0; j < d_ff; ++j) acc = fmaf(hr[j], dr[j], acc);
-    y[(size_t)row * d + i] = acc;
-}
-
 }  // namespace
 
 size_t ffn_workspace_bytes() {
@@ -1270,23 +1219,7 @@ bool ffn_can_fold(const FfnArgs& a) {
 hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {
     if (a.rows_cap == 0) return hipSuccess;
     const bool up = part != 2, down = part != 1;
-    if (a.dtype == BMOE_F32) {
-        const int64_t n1 = (int64_t)a.rows_cap * a.d_ff, n2 = (int64_t)a.rows_cap * a.d;
-        if (up) {
-            hipLaunchKernelGGL(ffn_f32_gateup_kernel, dim3((unsigned)ceil_div64(n1, 256)), dim3(256), 0, s,
-                               (const float*)a.a, (const float*)a.w_gate, (const float*)a.w_up, (float*)a.h,
-                               a.offsets, a.n_seg, a.rows_cap, a.d, a.d_ff, a.a_rows, a.a_count);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        if (down) {
-            hipLaunchKernelGGL(ffn_f32_down_kernel, dim3((unsigned)ceil_div64(n2, 256)), dim3(256), 0, s,
-                               (const float*)a.h, (const float*)a.w_down, (float*)a.y, a.offsets, a.n_seg,
-                               a.rows_cap, a.d, a.d_ff);
-            return hipGetLastError();
-        }
-        return hipSuccess;
-    }
+    if (a.dtype == BMOE_F32) return launch_ffn_f32(a, s, part);
     if (ffn_skinny_fits(a)) return launch_ffn_skinny(a, s, part);
     const int tile = ffn_tile(a);
     if (up) {

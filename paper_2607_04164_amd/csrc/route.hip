@@ -13,7 +13,7 @@
 //              waves split d; each wave loads its x columns straight into
 //              registers (all at once) and copies its W_router columns into
 //              its own LDS area, so the copy phase has no barrier;
-//        f32:  one (token, expert) dot product per thread;
+//        f32:  16 experts at a time on the fp32 MFMA, the waves splitting d;
 //        logits_in: copied.
 //   2. per token, a group of S lanes (S <= 16, chosen so that a wave's tokens
 //      fill it) holds the E logits, V <= 16 per lane; k+1 rounds of a
@@ -57,7 +57,7 @@ constexpr int kXdSlot = 16 * 1024;        // 64 router rows x 2 column halves x 
 constexpr int kXdPart = 2 * 16 * 64 * 4;  // partial tiles of the waves of the second half
 
 // LDS of the router columns (8 rows of d, four wave areas) and of the
-// partial logit tiles of waves 1..3
+// partial logit tiles of waves 1..3 (also the fp32 logits')
 __host__ __device__ inline size_t res_w_bytes(int d) { return (size_t)8 * d * 2; }
 constexpr size_t kResPartBytes = 3 * 16 * 16 * 4;
 
@@ -105,6 +105,7 @@ __host__ __device__ inline RouteSmem route_smem(int E, int d) {
     s.dummy_bytes = (MODE == MODE_BF16 || MODE == MODE_BF16_XD) ? 4 * 1024 : 0;
     s.ring_bytes = 0;
     if constexpr (MODE == MODE_BF16) s.ring_bytes = (size_t)RouteCfg<TB, NBLK, KW>::NSLOT * RouteCfg<TB, NBLK, KW>::SLOT;
+    if constexpr (MODE == MODE_F32) s.ring_bytes = kResPartBytes;
     if constexpr (MODE == MODE_BF16_RES) s.ring_bytes = res_w_bytes(d) + kResPartBytes;
     if constexpr (MODE == MODE_BF16_XD) s.ring_bytes = (size_t)xd_ns(KW) * kXdSlot + kXdPart;
     return s;
@@ -791,6 +792,69 @@ __device__ __forceinline__ void logits_bf16_xd(const RouteArgs& p, float* zs, ch
     }
 }
 
+// fp32 logits of 16 tokens on the fp32 MFMA, 16 experts at a time. The four
+// waves split d in units of 16 columns (lane group q takes columns 4q .. 4q+3
+// of a unit with one 16-byte load; MFMA e of the unit multiplies the columns
+// 4q + e, the same for both operands; a last half unit reads zeros in groups
+// 2 and 3), four units in flight; the partial tiles are added in wave order.
+// fp32 calls are small and bound by load latency: one dot product per thread,
+// a serial chain of uncoalesced loads, took 22.7 us for 64 tokens, d = 256,
+// 8 experts by the kernel trace; this takes 5.1 us.
+__device__ __forceinline__ void logits_f32(const RouteArgs& p, float* zs, int zstride, float* part, int t0) {
+    constexpr int U = 4;
+    const float* x = (const float*)p.x;
+    const float* w = (const float*)p.w;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int q = lane >> 4, r16 = lane & 15;
+    const int d = p.d, E = p.E;
+    const int nu = ceil_div(d, 16);
+    const int u0 = nu * wave / 4, u1 = nu * (wave + 1) / 4;
+    const float* xr = x + (size_t)min(t0 + r16, p.T - 1) * d + 4 * q;
+    for (int e0 = 0; e0 < E; e0 += 16) {
+        const int e = e0 + r16;
+        const float* wr = w + (size_t)min(e, E - 1) * d + 4 * q;
+        const float bz = (p.bias && e < E) ? p.bias[e] : 0.f;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int u = u0; u < u1; u += U) {
+            float4 a[U], b[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                // (every load is issued, from column 0 where there is no
+                // unit: a branch around it would cost its latency)
+                const int c = (u + j) * 16;
+                const bool in = u + j < u1 && c + 4 * q < d;
+                a[j] = *(const float4*)(xr + (in ? c : -4 * q));
+                b[j] = *(const float4*)(wr + (in ? c : -4 * q));
+                if (!in) a[j] = b[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j].x, b[j].x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j].y, b[j].y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j].z, b[j].z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j].w, b[j].w, acc, 0, 0, 0);
+            }
+        }
+        // D[4q + i][r16]: token 4q + i, expert e0 + r16
+        if (wave > 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[((wave - 1) * 16 + 4 * q + i) * 16 + r16] = acc[i];
+        }
+        __syncthreads();
+        if (wave == 0 && e < E) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int tl = 4 * q + i;
+                float v = acc[i];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) v += part[(k * 16 + tl) * 16 + r16];
+                zs[tl * zstride + e] = v + bz;
+            }
+        }
+        __syncthreads();  // the next experts rewrite the partial tiles
+    }
+}
+
 template <int MODE, int TB, int NBLK, int KW>
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs p) {
     extern __shared__ __align__(16) char smem[];
@@ -824,17 +888,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs p) {
     } else if constexpr (MODE == MODE_BF16_XD) {
         logits_bf16_xd<xd_nu(KW), xd_ns(KW)>(p, zs, ring, dummy, (float*)(ring + xd_ns(KW) * kXdSlot), t0);
     } else if constexpr (MODE == MODE_F32) {
-        const float* x = (const float*)p.x;
-        const float* w = (const float*)p.w;
-        for (int i = tid; i < BT * E; i += kRouteThreads) {
-            int tl = i / E, e = i % E;
-            int t = min(t0 + tl, T - 1);
-            const float* xr = x + (size_t)t * p.d;
-            const float* wr = w + (size_t)e * p.d;
-            float acc = 0.f;
-            for (int j = 0; j < p.d; ++j) acc = fmaf(xr[j], wr[j], acc);
-            zs[tl * sm.zstride + e] = acc + (p.bias ? p.bias[e] : 0.f);
-        }
+        logits_f32(p, zs, sm.zstride, (float*)ring, t0);
     } else {
         for (int i = tid; i < BT * E; i += kRouteThreads) {
             int tl = i / E, e = i % E;

@@ -1,0 +1,90 @@
+"""Edges of the kernels' tiles and of the rules that pick a kernel, against
+the CPU oracle (needs an MI355X): remainders, empty and one-row segments, the
+smallest sizes, and the sizes on either side of a rule. Tolerances are those
+of gpu_util."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import TOL, assert_close_rows, assert_gates, desc_of, dev_tensor, host_f32, to_storage  # noqa: F401
+from paper_2607_04164_amd import binding as B
+from paper_2607_04164_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B.load_library()
+
+
+def ffn_case(sizes, cap, d, f, dtype, seed, n_tokens=None):
+    """Random segments: offsets, storage-format arrays and the oracle's (y, h).
+    n_tokens: the rows are gathered from that many tokens."""
+    r = np.random.default_rng(seed)
+    n = len(sizes)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    N = int(offsets[-1])
+    x = to_storage(r.standard_normal((n_tokens or cap, d)).astype(np.float32), dtype)
+    rows = r.integers(0, n_tokens, cap).astype(np.int32) if n_tokens else None
+    ws = [to_storage((r.standard_normal(s) / np.sqrt(d)).astype(np.float32), dtype)
+          for s in ((n, f, d), (n, f, d), (n, d, f))]
+    wide = (lambda a: a) if dtype == "f32" else W.bf16_bits_to_f32
+    a = wide(x if rows is None else x[rows])
+    y, h = oracle.ffn(offsets, a[:max(N, 1)], *(wide(t) for t in ws), want_h=True)
+    return offsets, N, x, rows, ws, y, h
+
+
+def check_ffn(sizes, cap, d, f, dtype, seed=0, n_tokens=None, workspace=None, split_min_idle=None):
+    offsets, N, x, rows, ws, y, h = ffn_case(sizes, cap, d, f, dtype, seed, n_tokens)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    yg = torch.full((cap, d), -5.0, dtype=dt, device="cuda")
+    hg = torch.full((cap, f), -5.0, dtype=dt, device="cuda")
+    offs, w = torch.from_numpy(offsets).cuda(), [dev_tensor(t, dtype) for t in ws]
+    if rows is None:
+        B.ffn(offs, dev_tensor(x, dtype), *w, y=yg, h=hg, workspace=workspace, split_min_idle=split_min_idle)
+    else:
+        B.ffn_gather(offs, torch.from_numpy(rows).cuda(), dev_tensor(x, dtype), *w, y=yg, h=hg, workspace=workspace)
+    torch.cuda.synchronize()
+    assert_close_rows(host_f32(hg[:N]), h, dtype, "h")
+    assert_close_rows(host_f32(yg[:N]), y, dtype, "y")
+    assert bool((yg[N:] == -5.0).all()) and bool((hg[N:] == -5.0).all()), "rows past the last segment are not written"
+
+
+F32_FFN = [
+    # (segment sizes, spare rows, d, d_ff, tokens gathered from): one K unit
+    # for eight waves, tiles of exactly 32 rows and columns, remainders of 8
+    # columns and 1 row, more segments than a wave has lanes
+    ((1,), 0, 8, 8, None),
+    ((32, 0, 33, 31), 4, 72, 40, None),
+    ((64, 5), 0, 264, 104, 20),
+    (tuple(i % 4 for i in range(70)), 9, 32, 64, 11),
+    ((200, 0, 1), 55, 512, 32, None),
+]
+
+
+@pytest.mark.parametrize("sizes,spare,d,f,tokens", F32_FFN, ids=[f"seg{len(c[0])}-d{c[2]}-f{c[3]}" for c in F32_FFN])
+def test_f32_ffn_tiles(sizes, spare, d, f, tokens):
+    check_ffn(sizes, sum(sizes) + spare, d, f, "f32", n_tokens=tokens)
+
+
+@pytest.mark.parametrize("T,d,E,k", [(1, 8, 1, 1), (17, 24, 8, 2), (16, 264, 16, 4), (33, 72, 17, 3), (50, 40, 200, 9)])
+def test_f32_route(T, d, E, k):
+    """The fp32 gate: one and several blocks of 16 experts, a last half unit of d, ragged token tiles."""
+    cfg = W.LayerConfig("f32route", T=T, d=d, E=E, top_k=k, G=max(1, E // 2), d_ff=8, dtype="f32", zipf_s=1.0)
+    L = W.make_layer(cfg, 4, with_weights=False)
+    ref = oracle.route(L.f32("x"), L.f32("w_router"), L.bias, L.e2g, k, 0)
+    got = B.route(desc_of(cfg), dev_tensor(L.x, "f32"), dev_tensor(L.w_router, "f32"), torch.from_numpy(L.bias).cuda(),
+                  torch.from_numpy(L.e2g).cuda(), want_logits=True)
+    torch.cuda.synchronize()
+    zerr = np.abs(got["logits"].cpu().numpy().astype(np.float64) - ref["logits"]).max()
+    assert zerr < B.ROUTE_RECHECK_GAP / 4, f"fp32 logit error {zerr:.3e}"
+    for key in ("topk_idx", "slot_group"):
+        assert np.array_equal(got[key].cpu().numpy(), ref[key]), key
+    assert_gates(got["topk_w"].cpu().numpy(), ref["topk_w"], "topk_w")
+    assert_gates(got["slot_gate"].cpu().numpy(), ref["slot_gate"], "slot_gate")
