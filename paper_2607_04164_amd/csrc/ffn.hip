@@ -1173,7 +1173,13 @@ hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipS
         }
     }
     if (P > 0) {
-        const bool split = ws != nullptr && ws_bytes >= (size_t)2 * P * kSkSlotBytes;
+        // Whole tiles leave at most P - 1 workgroups without one in the last
+        // round, so tiles of at most min_idle K-steps are never split,
+        // whatever the offsets say: no workspace, and no launch of a fixup
+        // with nothing to do (4.7 us in a chain of launches; d or d_ff up to
+        // 48 K-steps: fine layer 564 -> 553 us).
+        const bool can = (int64_t)(P - 1) * (g.K / C::BK) > (int64_t)g.sk_min_idle * P;
+        const bool split = can && ws != nullptr && ws_bytes >= (size_t)2 * P * kSkSlotBytes;
         hipLaunchKernelGGL((grouped_gemm_dma_kernel<GATED, true>), dim3(P), dim3(kGemmThreads), 0, s, g,
                            split ? (char*)ws : (char*)nullptr);
         hipError_t e = hipGetLastError();
