@@ -270,7 +270,7 @@ bmoe_status brownout_moe_distill_mse(int32_t dtype, int32_t E, int32_t G, int32_
     if (!e2g || !w_freq || !y_expert || !y_united || !mse) return BMOE_ERR_NULL;
     if (!aligned16(y_expert) || !aligned16(y_united) || ((uintptr_t)mse & 7u) || ((uintptr_t)mse_total & 7u))
         return BMOE_ERR_ALIGN;
-    if (!workspace || workspace_bytes < (size_t)nb * G * sizeof(double)) return BMOE_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < bmoe::distill_ws_bytes(G, T)) return BMOE_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 7u) return BMOE_ERR_ALIGN;
     bmoe::DistillArgs a{e2g, w_freq, y_expert, y_united, mse, mse_total, workspace, E, G, T, d, dtype};
     return hip_status(bmoe::launch_distill_mse(a, (hipStream_t)stream));

@@ -147,10 +147,11 @@ struct DistillArgs {
     const void* y_united;   // [G*T, d]
     double* mse;            // [G]
     double* total;          // nullable
-    void* ws;               // distill_blocks(G, T) * G doubles
+    void* ws;               // distill_ws_bytes(G, T)
     int E, G, T, d, dtype;
 };
 int distill_blocks(int G, int T);
+size_t distill_ws_bytes(int G, int T);
 hipError_t launch_distill_mse(const DistillArgs& a, hipStream_t s);
 
 struct RouteArgs {

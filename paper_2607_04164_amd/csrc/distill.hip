@@ -20,16 +20,30 @@ namespace {
 
 constexpr int kDThreads = 256;
 
-// Members of group r (ascending expert index) into s_mem; returns the count.
-// Every thread of the (256-thread) workgroup must call it.
-__device__ __forceinline__ int group_members(const int32_t* e2g, int E, int r, int* s_mem, int* s_scan) {
-    const int tid = threadIdx.x;
+// Members of group r (ascending expert index) into s_mem, and with w their
+// routing frequencies into s_w; returns the count. Every thread of the
+// (256-thread) workgroup must call it. One round of loads and two barriers:
+// this runs before a workgroup's first load of data.
+__device__ __forceinline__ int group_members(const int32_t* e2g, const float* w, int E, int r, int* s_mem, float* s_w,
+                                             int* s_cnt) {
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const bool in = tid < E && e2g[tid] == r;
-    int n;
-    const int pos = block_exclusive_scan_256(in ? 1 : 0, s_scan, &n);
-    if (in) s_mem[pos] = tid;
+    const float wv = (w && tid < E) ? w[tid] : 0.f;
+    const unsigned long long m = __ballot(in);
+    if (lane == 0) s_cnt[wave] = __popcll(m);
     __syncthreads();
-    return n;
+    int pos = __popcll(m & ((1ull << lane) - 1ull)), n = 0;
+#pragma unroll
+    for (int v = 0; v < kDThreads / 64; ++v) {
+        if (v < wave) pos += s_cnt[v];
+        n += s_cnt[v];
+    }
+    if (in) {
+        s_mem[pos] = tid;
+        if (w) s_w[pos] = wv;
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(n);
 }
 
 template <typename V>
@@ -63,9 +77,9 @@ __global__ __launch_bounds__(kDThreads) void united_init_kernel(const int32_t* _
                                                                 int64_t nchunk) {
     constexpr int EPC = 16 / sizeof(V);
     __shared__ int s_mem[BMOE_MAX_EXPERTS];
-    __shared__ int s_scan[256];
+    __shared__ int s_cnt[kDThreads / 64];
     const int r = blockIdx.y, mat = blockIdx.z;
-    const int n = group_members(e2g, E, r, s_mem, s_scan);
+    const int n = group_members(e2g, nullptr, E, r, s_mem, nullptr, s_cnt);
     const V* src = mat == 0 ? s0 : mat == 1 ? s1 : s2;
     V* dst = mat == 0 ? d0 : mat == 1 ? d1 : d2;
     const int64_t per = nchunk * EPC;  // elements per matrix
@@ -109,13 +123,12 @@ __global__ __launch_bounds__(kDThreads) void united_init_kernel(const int32_t* _
 }
 
 // Alphas of Eq. 5 for the members of one group (equal weights when the
-// members' frequencies sum to zero), into s_alpha; every thread calls it.
-__device__ __forceinline__ void group_alphas(const float* w, const int* s_mem, int n, float* s_alpha) {
-    if (threadIdx.x == 0) {
-        double tot = 0.0;
-        for (int m = 0; m < n; ++m) tot += (double)w[s_mem[m]];
-        for (int m = 0; m < n; ++m) s_alpha[m] = tot > 0.0 ? (float)((double)w[s_mem[m]] / tot) : 1.f / (float)n;
-    }
+// members' frequencies s_w sum to zero), into s_alpha; every thread calls it.
+__device__ __forceinline__ void group_alphas(const float* s_w, int n, float* s_alpha) {
+    double tot = 0.0;
+    for (int m = 0; m < n; ++m) tot += (double)s_w[m];
+    for (int m = threadIdx.x; m < n; m += kDThreads)
+        s_alpha[m] = tot > 0.0 ? (float)((double)s_w[m] / tot) : 1.f / (float)n;
     __syncthreads();
 }
 
@@ -128,19 +141,21 @@ __global__ __launch_bounds__(kDThreads) void distill_partial_kernel(const int32_
                                                                     double* __restrict__ part) {
     constexpr int EPC = 16 / sizeof(V);
     __shared__ int s_mem[BMOE_MAX_EXPERTS];
-    __shared__ int s_scan[256];
+    __shared__ int s_cnt[kDThreads / 64];
+    __shared__ float s_w[BMOE_MAX_EXPERTS];
     __shared__ float s_alpha[BMOE_MAX_EXPERTS];
     __shared__ double s_red[kDThreads];
     const int r = blockIdx.y, nb = gridDim.x, b = blockIdx.x;
-    const int n = group_members(e2g, E, r, s_mem, s_scan);
-    group_alphas(w, s_mem, n, s_alpha);
+    const int n = group_members(e2g, w, E, r, s_mem, s_w, s_cnt);
+    group_alphas(s_w, n, s_alpha);
     const int nch = d / EPC;
     const int t0 = (int)((int64_t)T * b / nb), t1 = (int)((int64_t)T * (b + 1) / nb);
     const int nc = (t1 - t0) * nch;  // chunks of this workgroup (the host bounds T d / nb)
     double acc = 0.0;
     if (n > 0) {
         // two chunks per thread and step, every load of both issued before any
-        // is used; squares added in chunk order
+        // is used (four members' loads at once measured the same); squares
+        // added in chunk order
         constexpr int U = 2;
         for (int c0 = threadIdx.x; c0 < nc; c0 += U * kDThreads) {
             float tv[U][EPC], u[U][EPC];
@@ -192,30 +207,55 @@ __global__ __launch_bounds__(kDThreads) void distill_partial_kernel(const int32_
     if (threadIdx.x == 0) part[(size_t)r * nb + b] = s_red[0];
 }
 
-// mse[r] = (sum of group r's partials in slot order) / (T d); total = sum of
-// beta_r mse[r] in ascending r (beta_r: the members' frequency sum).
-__global__ __launch_bounds__(kDThreads) void distill_final_kernel(const int32_t* __restrict__ e2g, int E, int G,
-                                                                  const float* __restrict__ w,
-                                                                  const double* __restrict__ part, int nb, int T,
-                                                                  int d, double* __restrict__ mse,
-                                                                  double* __restrict__ total) {
+// mse[r] = (sum of group r's partials in a fixed order) / (T d); total = sum
+// of beta_r mse[r] in ascending r (beta_r: the members' frequency sum). One
+// workgroup, bound by latency: the partials, the map and the frequencies are
+// fetched together into LDS (one memory latency), then a wave takes a group
+// and adds its partials and frequencies over its lanes (lane i the entries i,
+// i + 64, .., then a tree). 15 groups of 68 partials: 23 -> 4.9 us (a thread
+// per group reading its partials and the map one after another).
+constexpr int kDMaxPart = 1024;  // G * distill_blocks <= 1024
+constexpr int kDFinal = 1024;    // threads
+__device__ __forceinline__ double wave_sum(double v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+__global__ __launch_bounds__(kDFinal) void distill_final_kernel(const int32_t* __restrict__ e2g, int E, int G,
+                                                                const float* __restrict__ w,
+                                                                const double* __restrict__ part, int nb, int T,
+                                                                int d, double* __restrict__ mse,
+                                                                double* __restrict__ total) {
+    __shared__ double s_part[kDMaxPart];
     __shared__ double s_wm[BMOE_MAX_EXPERTS];  // beta_r * mse_r
-    const int r = threadIdx.x;
-    if (r < G) {
-        double s = 0.0, beta = 0.0;
-        int n = 0;
-        for (int b = 0; b < nb; ++b) s += part[(size_t)r * nb + b];
-        for (int e = 0; e < E; ++e)
-            if (e2g[e] == r) {
-                beta += (double)w[e];
-                ++n;
-            }
-        const double m = n ? s / ((double)T * (double)d) : 0.0;
-        mse[r] = m;
-        s_wm[r] = beta * m;
+    __shared__ int s_e2g[BMOE_MAX_EXPERTS];
+    __shared__ float s_w[BMOE_MAX_EXPERTS];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    if (tid < G * nb) s_part[tid] = part[tid];
+    if (tid < E) {
+        s_e2g[tid] = e2g[tid];
+        s_w[tid] = w[tid];
     }
     __syncthreads();
-    if (r == 0 && total) {
+    for (int g = wave; g < G; g += kDFinal / 64) {
+        double s = 0.0, beta = 0.0;
+        int n = 0;
+        for (int b = lane; b < nb; b += 64) s += s_part[g * nb + b];
+        for (int e = lane; e < E; e += 64)
+            if (s_e2g[e] == g) {
+                beta += (double)s_w[e];
+                ++n;
+            }
+        s = wave_sum(s);
+        beta = wave_sum(beta);
+        if (__ballot(n > 0) == 0ull) s = 0.0;
+        if (lane == 0) {
+            const double m = s / ((double)T * (double)d);
+            mse[g] = m;
+            s_wm[g] = beta * m;
+        }
+    }
+    __syncthreads();
+    if (tid == 0 && total) {
         double tot = 0.0;
         for (int g = 0; g < G; ++g) tot += s_wm[g];
         *total = tot;
@@ -225,10 +265,15 @@ __global__ __launch_bounds__(kDThreads) void distill_final_kernel(const int32_t*
 }  // namespace
 
 int distill_blocks(int G, int T) {
-    // about four workgroups per CU (measured: 512 or 2048 in all were slower),
-    // at most one per token
-    int nb = (1024 + G - 1) / G;
+    // four workgroups per CU, all resident at once (measured: 512 or 2048 in
+    // all were slower), at most one per token
+    int nb = 1024 / G;
     return nb < T ? nb : T;
+}
+
+size_t distill_ws_bytes(int G, int T) {
+    const int nb = (1024 + G - 1) / G;  // (a little more than the partials of distill_blocks)
+    return (size_t)(nb < T ? nb : T) * G * sizeof(double);
 }
 
 hipError_t launch_united_init(const UnitedInitArgs& a, hipStream_t s) {
@@ -261,7 +306,7 @@ hipError_t launch_distill_mse(const DistillArgs& a, hipStream_t s) {
                            (const float*)a.y_expert, (const float*)a.y_united, a.T, a.d, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(distill_final_kernel, dim3(1), dim3(kDThreads), 0, s, a.e2g, a.E, a.G, a.w, part, nb, a.T,
+    hipLaunchKernelGGL(distill_final_kernel, dim3(1), dim3(kDFinal), 0, s, a.e2g, a.E, a.G, a.w, part, nb, a.T,
                        a.d, a.mse, a.total);
     return hipGetLastError();
 }
