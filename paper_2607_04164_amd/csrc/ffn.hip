@@ -3,20 +3,21 @@
 //   h = silu(A W_gate[s]^T) * (A W_up[s]^T)     (gate/up fused, one pass over A)
 //   y = h W_down[s]^T
 //
-// bf16 path: one grouped-GEMM kernel template, 256 threads (4 waves, 2x2),
-// 32x32x16 bf16 MFMA with fp32 accumulation, A and B tiles double-buffered in
-// LDS with padded rows (conflict-free 128-bit fragment reads), global loads of
-// the next K-step in flight while the current one runs on the matrix cores.
+// bf16 path, above the skinny kernels' batch size: the persistent kernel with
+// direct-to-LDS copies (grouped_gemm_dma_kernel, below). K too short and ragged
+// for it (at most 128 columns, not whole 64-column K-steps) takes
+// grouped_gemm_kernel: 256 threads (4 waves, 2x2), 32x32x16 bf16 MFMA with fp32
+// accumulation, A and B tiles double-buffered in LDS with padded rows
+// (conflict-free 128-bit fragment reads), global loads of the next K-step in
+// flight while the current one runs on the matrix cores.
 //   gate/up: BM=128, BN=128 columns of BOTH W_gate and W_up (each wave 64x64 of
 //            each), epilogue silu(g)*u -> bf16 h;
 //   down:    BM=128, BN=256 (each wave 64x128), epilogue -> bf16 y.
-// Both epilogues stage the tile through LDS and store 128-bit row chunks.
-// Tile schedule without a host sync: the grid covers the worst case
-// (ceil(rows_cap/BM) + n_seg M-tiles times the N-tiles); every workgroup
-// rebuilds the per-segment M-tile prefix from the device offsets, maps its
-// (XCD-swizzled) id to (segment, N-tile, M-tile) with M fastest, so the
-// M-tiles that share a weight panel run together on one XCD, and workgroups
-// past the real tile count exit at once.
+// Its grid covers the worst case (ceil(rows_cap/BM) + n_seg M-tiles times the
+// N-tiles); every workgroup rebuilds the per-segment M-tile prefix from the
+// device offsets (no host sync), maps its (XCD-swizzled) id to (segment,
+// N-tile, M-tile) with M fastest, and workgroups past the real tile count exit
+// at once.
 //
 // fp32 layers: ffn_f32.hip.
 #include <cstdlib>
@@ -322,10 +323,9 @@ hipError_t launch_gemm(const GemmParams& g, hipStream_t s) {
 // with fp32 accumulators, K-step 64 through a two-slot LDS ring filled by
 // global_load_lds_dwordx4.
 //
-// Work distribution. Without a workspace every workgroup computes one tile.
-// With one (stream-K), the grid is one workgroup per CU: full rounds of one
-// tile per workgroup, then the K-steps of the remaining tiles (between one
-// and two rounds' worth) are split evenly across the workgroups. A workgroup
+// Work distribution: one workgroup per CU, rounds of one tile per workgroup.
+// With a workspace (stream-K) the K-steps of the last tiles may be split evenly
+// across the workgroups instead. A workgroup
 // whose share starts or ends inside a tile writes that piece's fp32
 // accumulators to its workspace slot, and a second kernel sums the pieces of
 // each split tile in K order and applies the epilogue. No workgroup ever
@@ -339,8 +339,11 @@ constexpr int kSkPartBytes = 256 * 256 * 4;  // fp32 accumulators of one tile pi
 // time) do not all start on the same memory channel
 constexpr int kSkSlotBytes = kSkPartBytes + 1280;
 
-template <bool GATED>
+// VAR: the kernel that also takes half tiles and a ragged last K-step (see
+// gemm_var_pays); the other one has neither.
+template <bool GATED, bool VAR = false>
 struct DmaCfg {
+    static constexpr bool kVar = VAR;
     static constexpr int BM = 256, BK = kDmaBK, KC = BK / 8;  // KC: 16-byte chunks per row
     static constexpr int SUB = BK / 16;                       // MFMA sub-steps per K-step
     static constexpr int BN = GATED ? 128 : 256;              // output columns per matrix
@@ -362,7 +365,7 @@ struct DmaCfg {
     static constexpr int HSTG = 16 * SROW * 2;
     static constexpr int STG_OFF = RING;
     static constexpr int SCHED_OFF = STG_OFF + 4 * HSTG;                 // schedule arrays after them
-    static constexpr int SCHED = (256 + 3 * BMOE_MAX_EXPERTS + 1) * 4;
+    static constexpr int SCHED = 2 * 4 * 8 + (4 * BMOE_MAX_EXPERTS + 1) * 4;
     static constexpr int SMEM = SCHED_OFF + SCHED;
     static constexpr int CPR = WTN / 8;                                   // 16-byte chunks per output row
     static constexpr int NACC4 = NMAT * MB * NB * 4;                      // float4 accumulators per lane
@@ -399,16 +402,25 @@ struct DmaSrc {
     int a_zero;
 };
 
-// DMA instruction i of the wave's share of a K-step: instructions 0..A_DMA-1
-// fill A rows, the rest B rows; instruction i of wave w fills ROWS_PER_DMA
-// consecutive rows (1 KB of LDS). kb: byte offset of the K-step in a row.
+// First A row that copy instruction i of wave w fills. With half tiles, the
+// first half of the four waves' instructions fill a half tile's rows; without,
+// a wave's share is 64 neighbouring rows.
 template <class C>
+__device__ __forceinline__ int dma_copy_row(int wave, int i) {
+    constexpr int H = C::A_DMA / 2;
+    return (C::kVar ? i / H * 4 * H + wave * H + i % H : wave * 2 * H + i) * C::ROWS_PER_DMA;
+}
+
+// DMA instruction i of the wave's share of a K-step with NA copies of A rows:
+// instructions 0..NA-1 fill A rows, the rest B rows; each fills ROWS_PER_DMA
+// consecutive rows (1 KB of LDS). kb: byte offset of the K-step in a row.
+template <class C, int NA>
 __device__ __forceinline__ void dma_one(const DmaSrc<C>& src, uint32_t stage_lds, int wave, int kb, int i) {
-    if (i < C::A_DMA) {
+    if (i < NA) {
         const char* base = (src.a_zero >> i) & 1 ? (const char*)g_zero_rows : src.a_base;
-        dma16s(base + kb, src.a_off[i], stage_lds + ((wave * C::A_DMA + i) * C::ROWS_PER_DMA) * C::ROW_BYTES);
+        dma16s(base + kb, src.a_off[i], stage_lds + dma_copy_row<C>(wave, i) * C::ROW_BYTES);
     } else {
-        const int j = i - C::A_DMA;
+        const int j = i - NA;
         dma16s(src.b_base + kb, src.b_off[j],
                stage_lds + C::A_STAGE + ((wave * C::B_DMA + j) * C::ROWS_PER_DMA) * C::ROW_BYTES);
     }
@@ -417,24 +429,20 @@ __device__ __forceinline__ void dma_one(const DmaSrc<C>& src, uint32_t stage_lds
 template <class C>
 __device__ __forceinline__ void dma_stage(const DmaSrc<C>& src, uint32_t stage_lds, int wave, int kb) {
 #pragma unroll
-    for (int i = 0; i < C::DMA_PER_STAGE; ++i) dma_one<C>(src, stage_lds, wave, kb, i);
+    for (int i = 0; i < C::DMA_PER_STAGE; ++i) dma_one<C, C::A_DMA>(src, stage_lds, wave, kb, i);
 }
 
-// First tile row of 32-row block mb of wave row wm. (Interleaving the two
-// wave rows' blocks and leaving out the MFMAs of blocks wholly past a
-// segment's end made the partly filled last tiles of the segments run ahead
-// of the others: the workgroups of an XCD then drifted apart along K, and the
-// gate/up GEMM's L2 misses doubled. Every tile keeps the full MFMA work.)
-template <class C>
-__device__ __forceinline__ int dma_arow(int wm, int mb) { return wm * C::WTM + mb * 32; }
+// First tile row of 32-row block mb of wave row wm, in a tile of mbs blocks
+// per wave (64 mbs rows).
+__device__ __forceinline__ int dma_arow(int wm, int mb, int mbs) { return (wm * mbs + mb) * 32; }
 
-template <class C>
+template <class C, int MB>
 __device__ __forceinline__ void dma_frags(uint4 (&af)[C::MB], uint4 (&bf)[C::NMAT][C::NB], const char* stage,
                                           int wm, int wn, int lane, int kk) {
     const int c = kk * 2 + (lane >> 5), l32 = lane & 31;
 #pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
-        af[mb] = *(const uint4*)(stage + lds_off<C>(dma_arow<C>(wm, mb) + l32, c));
+    for (int mb = 0; mb < MB; ++mb)
+        af[mb] = *(const uint4*)(stage + lds_off<C>(dma_arow(wm, mb, MB) + l32, c));
 #pragma unroll
     for (int mat = 0; mat < C::NMAT; ++mat)
 #pragma unroll
@@ -443,7 +451,7 @@ __device__ __forceinline__ void dma_frags(uint4 (&af)[C::MB], uint4 (&bf)[C::NMA
 }
 
 // Fragment read r of a sub-step (r < NMAT*NB: B fragments, then A).
-template <class C>
+template <class C, int MB>
 __device__ __forceinline__ void frag_read(uint4 (&ga)[C::MB], uint4 (&gb)[C::NMAT][C::NB], const char* stage, int wm,
                                           int wn, int l32, int c, int r) {
     if (r < C::NMAT * C::NB) {
@@ -451,99 +459,203 @@ __device__ __forceinline__ void frag_read(uint4 (&ga)[C::MB], uint4 (&gb)[C::NMA
         gb[rm][rn] = *(const uint4*)(stage + C::A_STAGE + lds_off<C>(rm * C::BN + wn * C::WTN + rn * 32 + l32, c));
     } else {
         const int ra = r - C::NMAT * C::NB;
-        ga[ra] = *(const uint4*)(stage + lds_off<C>(dma_arow<C>(wm, ra) + l32, c));
+        ga[ra] = *(const uint4*)(stage + lds_off<C>(dma_arow(wm, ra, MB) + l32, c));
     }
 }
 
-// The MFMAs of one sub-step with, between them, the fragment reads of RD
-// later sub-steps (RD = 1: one read after every second MFMA; RD = 2: one
-// after every MFMA, set 1 first) and ND of the wave's copies of a K-step
-// (DMA instructions d0 .. d0 + ND - 1), one after every (NM / ND)-th MFMA.
-// (Issuing a sub-step's copies after each of its first MFMAs instead
-// measured 1-3 % slower: the copies must be spread.)
-template <class C, int RD, int ND>
+// The MFMAs of one sub-step (MB row blocks per wave) with, between them, the
+// fragment reads of RD later sub-steps (spread evenly, set 1 first) and ND of
+// the wave's copies of a K-step (DMA instructions d0 .. d0 + ND - 1 of NA A
+// copies and the B copies). (Issuing a sub-step's copies after each of its
+// first MFMAs instead measured 1-3 % slower: the copies must be spread.)
+template <class C, int MB, int RD, int ND, int NA>
 __device__ __forceinline__ void mfmas_ops(f32x16 (&acc)[C::NMAT][C::MB][C::NB], const uint4 (&af)[C::MB],
                                           const uint4 (&bf)[C::NMAT][C::NB], uint4 (&ga1)[C::MB],
                                           uint4 (&gb1)[C::NMAT][C::NB], const char* st1, int kk1,
                                           uint4 (&ga2)[C::MB], uint4 (&gb2)[C::NMAT][C::NB], const char* st2,
                                           int kk2, int wm, int wn, int lane, const DmaSrc<C>& src,
                                           uint32_t dma_lds, int wave, int kb, int d0) {
-    constexpr int NM = C::NMAT * C::MB * C::NB, NR = C::MB + C::NMAT * C::NB;
-    static_assert(2 * NR == NM && C::DMA_PER_STAGE == NM, "one read and one copy per two MFMAs");
-    static_assert(ND >= 0 && ND <= NM / 2, "at most one copy per two MFMAs");
-    constexpr int STEP = ND > 0 ? NM / ND : NM;
+    constexpr int NM = C::NMAT * MB * C::NB, NR = MB + C::NMAT * C::NB;
     const int l32 = lane & 31, c1 = kk1 * 2 + (lane >> 5), c2 = kk2 * 2 + (lane >> 5);
 #pragma unroll
     for (int q = 0; q < NM; ++q) {
         const int mb = q / (C::NMAT * C::NB), mat = (q / C::NB) % C::NMAT, nb = q % C::NB;
         acc[mat][mb][nb] = mfma32(af[mb], bf[mat][nb], acc[mat][mb][nb]);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (RD == 2) {
-            if (q < NR) frag_read<C>(ga1, gb1, st1, wm, wn, l32, c1, q);
-            else frag_read<C>(ga2, gb2, st2, wm, wn, l32, c2, q - NR);
-        } else if constexpr (RD == 1) {
-            if (q & 1) frag_read<C>(ga1, gb1, st1, wm, wn, l32, c1, q >> 1);
+#pragma unroll
+        for (int r = q * RD * NR / NM; r < (q + 1) * RD * NR / NM; ++r) {
+            if (r < NR) frag_read<C, MB>(ga1, gb1, st1, wm, wn, l32, c1, r);
+            else frag_read<C, MB>(ga2, gb2, st2, wm, wn, l32, c2, r - NR);
         }
-        if constexpr (ND > 0) {
-            if (q % STEP == 0 && q / STEP < ND) dma_one<C>(src, dma_lds, wave, kb, d0 + q / STEP);
-        }
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+            if (q == (ND <= NM ? i * (NM / (ND > 0 ? ND : 1)) : i * NM / ND))
+                dma_one<C, NA>(src, dma_lds, wave, kb, d0 + i);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// ---- tile schedule: per-segment M-tile prefix in LDS, computed from the
-// device offsets by every workgroup (the host does not read the offsets)
+// ---- tile schedule, computed in LDS from the device offsets by every
+// workgroup (the host does not read the offsets)
+//
+// A segment's rows make whole 256-row tiles and a tail. A tail of more than
+// 128 rows takes a whole tile too, a shorter one a tile of half the height
+// (two 32-row blocks per wave instead of four), which costs about 0.6 of a
+// whole one (its B rows are still copied and read from LDS in full). The half
+// tiles come after all whole ones: among them, cheaper tiles ran ahead, the
+// workgroups of an XCD drifted apart along K and the L2 misses of the gate/up
+// GEMM doubled. (Heights of 64 and 192 rows too would save no more on the
+// layers' segments, and two more copies of the K loop spilled registers.)
+// A half tile reads its segment's weights again. When the segments that have
+// whole tiles too make that more than kRereadMax (what the last-level cache
+// may still hold), their tails stay whole tiles among the others:
+// Mixtral-shaped, 235 MB per segment of gate/up weights.
+// With the stream-K split every tile is whole (equal K-steps cost the same).
+constexpr int64_t kRereadMax = (int64_t)256 << 20;
+
 struct TileSched {
-    int* s_mt;   // [n_seg + 1] first M-tile of each segment
-    int* s_beg;  // [n_seg] first row of each segment
-    int* s_end;  // [n_seg] end row of each segment
-    int NT, total_mt;
+    int* s_mt;    // [n_seg + 1] first whole M-tile of each segment
+    int* s_beg;   // [n_seg] first row of each segment
+    int* s_end;   // [n_seg] end row of each segment
+    int* s_half;  // segments with a half tile, in order
+    int NT, full_mt, half_mt;  // N-tiles, whole M-tiles, half M-tiles
+    __device__ __forceinline__ int total() const { return (full_mt + half_mt) * NT; }
 };
 
 struct TileCoord {
     int s, m0, m_end, n0;
+    bool half;  // 128 rows instead of 256
 };
 
-// Returns the schedule; ends with a barrier. The arrays must not be written
-// while a workgroup uses them (they live outside the ring and staging area).
-__device__ __forceinline__ TileSched tile_sched(const GemmParams& p, char* sched_lds, int BM, int BN) {
+// Inclusive scan over the 256 threads of a workgroup (total: the sum). buf: 4
+// values of LDS that no other scan of the kernel uses; one barrier.
+__device__ __forceinline__ uint64_t block_inclusive_scan(uint64_t v, uint64_t* buf, uint64_t& total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint64_t o = __shfl_up((unsigned long long)v, off);
+        if (lane >= off) v += o;
+    }
+    if (lane == kWave - 1) buf[wave] = v;
+    __syncthreads();
+    total = 0;
+    uint64_t before = 0;
+#pragma unroll
+    for (int w = 0; w < kGemmThreads / kWave; ++w) {
+        if (w < wave) before += buf[w];
+        total += buf[w];
+    }
+    return v + before;
+}
+
+// Work of P persistent workgroups: F rounds of one tile each (round r, tile
+// r*P + w; the last round may be partial), then, split by K-steps, the tiles
+// [F*P, total): each workgroup gets `share` consecutive K-steps of those.
+// The split moves two fp32 tile pieces per workgroup through memory and
+// restarts the pipeline per piece, so it is used (with a workspace) only when
+// whole tiles would leave the workgroups idle for more than min_idle K-steps
+// on average (the caller's threshold, kSkMinIdle by default).
+constexpr int kSkMinIdle = 48;
+constexpr int kSkMinShare = 8;  // K-steps: the shortest piece worth a pipeline restart
+struct SkSplit {
+    int F, W, share;
+};
+__device__ __forceinline__ SkSplit sk_split(int total, int nk, int P, bool can_split, int min_idle) {
+    SkSplit k;
+    const int rounds = ceil_div(total, P);
+    const int64_t idle = (int64_t)(rounds * P - total) * nk;  // K-steps, summed over workgroups
+    if (!can_split || total == 0 || idle <= (int64_t)min_idle * P) {
+        k.F = rounds;
+        k.W = 0;
+        k.share = 1;
+    } else {
+        // split only the last partial round when its K-steps still give every
+        // workgroup a piece of kSkMinShare or more (fewer split tiles, fewer
+        // pieces through memory); otherwise the last one to two rounds
+        const int full = total / P;
+        const int64_t rest = (int64_t)(total - full * P) * nk;
+        k.F = rest >= (int64_t)kSkMinShare * P ? full : max(0, full - 1);
+        k.W = (total - k.F * P) * nk;
+        k.share = ceil_div(k.W, P);
+    }
+    return k;
+}
+
+// Returns the schedule and the split; ends with a barrier. The arrays must not
+// be written while a workgroup uses them (they live outside the ring and
+// staging area).
+template <class C>
+__device__ __forceinline__ TileSched tile_sched(const GemmParams& p, char* sched_lds, int P, bool can_split,
+                                                SkSplit& sk) {
     TileSched t;
-    int* s_scan = (int*)sched_lds;
-    t.s_mt = s_scan + 256;
+    uint64_t* buf = (uint64_t*)sched_lds;  // two scans' wave totals
+    t.s_half = (int*)(sched_lds + 2 * 4 * 8);
+    t.s_mt = t.s_half + BMOE_MAX_EXPERTS;
     t.s_beg = t.s_mt + BMOE_MAX_EXPERTS + 1;
     t.s_end = t.s_beg + BMOE_MAX_EXPERTS;
     const int tid = threadIdx.x;
-    int cnt = 0;
+    int rows = 0;
     if (tid < p.n_seg) {
         const int beg = min(max(p.offsets[tid], 0), p.rows_cap);
         const int end = min(max(p.offsets[tid + 1], beg), p.rows_cap);
         t.s_beg[tid] = beg;
         t.s_end[tid] = end;
-        cnt = ceil_div(end - beg, BM);
+        rows = end - beg;
     }
-    int total_mt;
-    const int ex = block_exclusive_scan_256(cnt, s_scan, &total_mt);
-    if (tid < p.n_seg) t.s_mt[tid] = ex;
-    if (tid == 0) t.s_mt[p.n_seg] = total_mt;
+    t.NT = ceil_div(p.N, C::BN);
+    const int whole = ceil_div(rows, C::BM);  // with the tail as a whole tile
+    bool half = C::kVar && rows % C::BM > 0 && rows % C::BM <= C::BM / 2;
+    uint64_t total;
+    uint64_t incl = block_inclusive_scan((uint64_t)(uint32_t)whole | (uint64_t)(half && rows > C::BM ? 1 : 0) << 32, buf,
+                                         total);
+    sk = sk_split(__builtin_amdgcn_readfirstlane((int)(uint32_t)total) * t.NT, ceil_div(p.K, C::BK), P, can_split,
+                  p.sk_min_idle);
+    uint32_t mt = whole;
+    if constexpr (C::kVar) {
+        const int64_t reread = (int64_t)(total >> 32) * C::NMAT * p.N * p.K * 2;
+        if (sk.W > 0 || (rows > C::BM && reread > kRereadMax)) half = false;
+        mt -= half ? 1 : 0;
+        incl = block_inclusive_scan((uint64_t)mt | (uint64_t)(half ? 1 : 0) << 32, buf + 4, total);
+    }
+    t.full_mt = __builtin_amdgcn_readfirstlane((int)(uint32_t)total);
+    t.half_mt = C::kVar ? __builtin_amdgcn_readfirstlane((int)(total >> 32)) : 0;
+    if (tid < p.n_seg) {
+        t.s_mt[tid] = (int)((uint32_t)incl - mt);
+        if (half) t.s_half[(int)(incl >> 32) - 1] = tid;
+    }
+    if (tid == 0) t.s_mt[p.n_seg] = t.full_mt;
+    // with no split, rounds of every tile
+    if (sk.W == 0) sk.F = ceil_div(t.total(), P);
     __syncthreads();
-    t.total_mt = __builtin_amdgcn_readfirstlane(total_mt);
-    t.NT = ceil_div(p.N, BN);
     return t;
 }
 
-// Tile L of the schedule: segments in order; inside a segment, groups of
-// kGroupM M-tiles with N-tiles outer, so that the workgroups that run
-// together on one XCD share A and B panels in L2. The values come from LDS;
-// readfirstlane keeps them (and the copy bases) in SGPRs.
-__device__ __forceinline__ TileCoord tile_coord(const TileSched& t, int n_seg, int L, int BM, int BN) {
+// Tile L of the schedule. Whole tiles: segments in order; inside a segment,
+// groups of kGroupM M-tiles with N-tiles outer, so that the workgroups that
+// run together on one XCD share A and B panels in L2. Then the half tiles, the
+// N-tiles of a segment together. The values come from LDS; readfirstlane
+// keeps them (and the copy bases) in SGPRs.
+template <class C>
+__device__ __forceinline__ TileCoord tile_coord(const TileSched& t, int n_seg, int L) {
+    constexpr int BM = C::BM, BN = C::BN;
     const int NT = t.NT;
+    TileCoord c;
+    if (C::kVar && L >= t.full_mt * NT) {
+        const int j = L - t.full_mt * NT, i = j / NT;
+        c.s = __builtin_amdgcn_readfirstlane(t.s_half[i]);
+        const int beg = __builtin_amdgcn_readfirstlane(t.s_beg[c.s]);
+        c.m_end = __builtin_amdgcn_readfirstlane(t.s_end[c.s]);
+        c.m0 = beg + (c.m_end - beg) / BM * BM;
+        c.n0 = (j - i * NT) * BN;
+        c.half = true;
+        return c;
+    }
     int lo = 0, hi = n_seg - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (t.s_mt[mid] * NT <= L) lo = mid;
         else hi = mid - 1;
     }
-    TileCoord c;
     c.s = __builtin_amdgcn_readfirstlane(lo);
     const int mts = __builtin_amdgcn_readfirstlane(t.s_mt[c.s + 1] - t.s_mt[c.s]);
     const int local = L - __builtin_amdgcn_readfirstlane(t.s_mt[c.s]) * NT;
@@ -553,6 +665,7 @@ __device__ __forceinline__ TileCoord tile_coord(const TileSched& t, int n_seg, i
     c.m0 = __builtin_amdgcn_readfirstlane(t.s_beg[c.s]) + mt * BM;
     c.m_end = __builtin_amdgcn_readfirstlane(t.s_end[c.s]);
     c.n0 = nt * BN;
+    c.half = false;
     return c;
 }
 
@@ -576,8 +689,8 @@ __device__ __forceinline__ void dma_sources(DmaSrc<C>& src, const GemmParams& p,
     int a_zero = 0;
 #pragma unroll
     for (int i = 0; i < C::A_DMA; ++i) {
-        const int r = (wave * C::A_DMA + i) * C::ROWS_PER_DMA + lrow;
-        const bool z = zero_ok && tc.m0 + (wave * C::A_DMA + i) * C::ROWS_PER_DMA >= tc.m_end;
+        const int r = dma_copy_row<C>(wave, i) + lrow;
+        const bool z = zero_ok && tc.m0 + r - lrow >= tc.m_end;
         a_zero |= z ? 1 << i : 0;
         const int row = gathered_row(p.a_rows, p.a_count, min(tc.m0 + r, tc.m_end - 1));
         src.a_off[i] = z ? (uint32_t)(lchk << 4)
@@ -596,6 +709,40 @@ __device__ __forceinline__ void dma_sources(DmaSrc<C>& src, const GemmParams& p,
     }
 }
 
+// Columns of the last K-step when K is not whole K-steps (else 0). The copies
+// of that K-step repeat its first chunk in place of the chunks past the row's
+// end (which may be past the tensor's), and once they have landed the
+// workgroup zeroes the A rows' (tail_zero), so their products vanish.
+template <class C>
+__device__ __forceinline__ int tail_cols(const GemmParams& p) { return C::kVar ? p.K % C::BK : 0; }
+
+template <class C>
+__device__ __forceinline__ void dma_tail(DmaSrc<C>& src, int tv, int wave, int lane_in) {
+    int lane = lane_in;
+    asm volatile("" : "+v"(lane));
+    const int lrow = lane / C::KC, lchk = lane % C::KC;
+#pragma unroll
+    for (int i = 0; i < C::A_DMA; ++i) {
+        const int c = lchk ^ swz<C::KC>(dma_copy_row<C>(wave, i) + lrow);
+        if (!((src.a_zero >> i) & 1) && c * 8 >= tv) src.a_off[i] -= c << 4;
+    }
+#pragma unroll
+    for (int i = 0; i < C::B_DMA; ++i) {
+        const int c = lchk ^ swz<C::KC>((wave * C::B_DMA + i) * C::ROWS_PER_DMA + lrow);
+        if (c * 8 >= tv) src.b_off[i] -= c << 4;
+    }
+}
+
+// Zeros the chunks past the tv columns of the last K-step in the A rows of
+// its ring slot (all copies landed); ends with a barrier.
+template <class C>
+__device__ __forceinline__ void tail_zero(char* stage, int tv) {
+    static_assert(C::BM == kGemmThreads, "one row per thread");
+    for (int c = tv / 8; c < C::KC; ++c) *(uint4*)(stage + lds_off<C>(threadIdx.x, c)) = make_uint4(0, 0, 0, 0);
+    lds_reads_done();  // (LDS writes too)
+    wg_barrier();
+}
+
 // The copies of K-steps ka and ka+1 (when the item has two) into the ring's
 // two slots; the ring must be free (every wave done reading it).
 template <class C>
@@ -611,7 +758,7 @@ __device__ __forceinline__ void ksteps_prologue(const DmaSrc<C>& src, char* smem
 // counter is not relied on to order the copies before later stores).
 enum { kAfterNone = 0, kAfterStores = 1 };
 
-// K-steps [ka, kb) of one tile into acc (which the caller zeroed), after
+// K-steps [ka, kb) of one tile of 64 MB rows into acc (which the caller zeroed), after
 // their first two K-steps' copies were issued (ksteps_prologue, or the
 // previous item's last K-steps). K-step kt lives in ring slot (kt + s0) & 1.
 // The next item (tile tc2, K-steps [nka, nkb); nka == nkb: none) has its
@@ -619,9 +766,12 @@ enum { kAfterNone = 0, kAfterStores = 1 };
 // item's own copies are all issued, src is set to the next item's sources
 // and its K-steps nka and nka+1 go into the slots this item's last two
 // K-steps free, so they arrive while this item's results go out (an item of
-// one K-step copies the next item's first K-step after its loop). Ends with
-// a barrier; src then holds the next item's sources.
-template <class C, bool GATED>
+// one K-step copies the next item's first K-step after its loop); they take
+// the copies of a whole tile's rows whatever the next item's height. Ends with
+// a barrier; src then holds the next item's sources. K that is not whole
+// K-steps: items are whole tiles of at least three K-steps (launch_gemm_dma),
+// so the copies of the last one are issued here, not by the previous item.
+template <class C, bool GATED, int MB>
 __device__ __forceinline__ void tile_ksteps(f32x16 (&acc)[C::NMAT][C::MB][C::NB], DmaSrc<C>& src, char* smem,
                                             int ka, int kb, int wave, int lane, int after, int s0,
                                             const GemmParams& p, const TileCoord& tc2, int nka, int nkb) {
@@ -647,42 +797,54 @@ __device__ __forceinline__ void tile_ksteps(f32x16 (&acc)[C::NMAT][C::MB][C::NB]
     // slot; sub-steps 1-3 issue the copies of K-step kt+2 (6, 5, 5); after
     // sub-step 2 a wait for this wave's older copies and a second barrier
     // make K-step kt+1 resident; sub-step 3 reads its sub-steps 0 and 1.
-    dma_frags<C>(af[0], bf[0], smem + (s0 & 1) * C::STAGE, wm, wn, lane, 0);
-    dma_frags<C>(af[1], bf[1], smem + (s0 & 1) * C::STAGE, wm, wn, lane, 1);
-    // K-step kt; with DMA, the copies of K-step kbyte / (BK * 2) of src go
-    // into its slot once the slot is free
-    auto kstep = [&](int kt, auto with_dma, int kbyte) {
+    dma_frags<C, MB>(af[0], bf[0], smem + (s0 & 1) * C::STAGE, wm, wn, lane, 0);
+    dma_frags<C, MB>(af[1], bf[1], smem + (s0 & 1) * C::STAGE, wm, wn, lane, 1);
+    const int tv = tail_cols<C>(p);
+    // K-step kt; the copies of K-step kbyte / (BK * 2) of src (na A copies)
+    // go into its slot once the slot is free. before_tail: the next K-step is
+    // this tile's ragged last one.
+    auto kstep = [&](int kt, auto na, bool before_tail, int kbyte) {
         const DmaSrc<C>& cs = src;
-        constexpr bool DMA = decltype(with_dma)::value;
+        constexpr int NA = decltype(na)::value;
         const int slot = (kt + s0) & 1;
         const char* cur = smem + slot * C::STAGE;
-        const char* nxt = smem + (slot ^ 1) * C::STAGE;
+        char* nxt = smem + (slot ^ 1) * C::STAGE;
         const uint32_t dma_lds = lds0 + slot * C::STAGE;
         const int kb = kbyte;
-        constexpr int D1 = 6, D2 = 5, D3 = C::DMA_PER_STAGE - D1 - D2;
+        constexpr int ND = NA + C::B_DMA, D1 = (ND + 2) / 3, D2 = (ND - D1 + 1) / 2, D3 = ND - D1 - D2;
         __builtin_amdgcn_sched_barrier(0);
-        mfmas_ops<C, 2, 0>(acc, af[0], bf[0], af[2], bf[2], cur, 2, af[3], bf[3], cur, 3, wm, wn, lane, cs,
-                           dma_lds, wave, kb, 0);
+        mfmas_ops<C, MB, 2, 0, NA>(acc, af[0], bf[0], af[2], bf[2], cur, 2, af[3], bf[3], cur, 3, wm, wn, lane, cs,
+                                   dma_lds, wave, kb, 0);
         __builtin_amdgcn_sched_barrier(0);
         lds_reads_done();
         wg_barrier();  // the slot is free
         __builtin_amdgcn_sched_barrier(0);
-        mfmas_ops<C, 0, DMA ? D1 : 0>(acc, af[1], bf[1], af[1], bf[1], cur, 0, af[1], bf[1], cur, 0, wm, wn, lane,
-                                      cs, dma_lds, wave, kb, 0);
+        mfmas_ops<C, MB, 0, D1, NA>(acc, af[1], bf[1], af[1], bf[1], cur, 0, af[1], bf[1], cur, 0, wm, wn, lane, cs,
+                                    dma_lds, wave, kb, 0);
         __builtin_amdgcn_sched_barrier(0);
-        mfmas_ops<C, 0, DMA ? D2 : 0>(acc, af[2], bf[2], af[2], bf[2], cur, 0, af[2], bf[2], cur, 0, wm, wn, lane,
-                                      cs, dma_lds, wave, kb, D1);
+        mfmas_ops<C, MB, 0, D2, NA>(acc, af[2], bf[2], af[2], bf[2], cur, 0, af[2], bf[2], cur, 0, wm, wn, lane, cs,
+                                    dma_lds, wave, kb, D1);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (DMA) wait_vmcnt<D1 + D2>();
-        else wait_vmcnt<0>();
+        wait_vmcnt<D1 + D2>();
         wg_barrier();  // the next K-step is resident
+        if (C::kVar && before_tail) tail_zero<C>(nxt, tv);
         __builtin_amdgcn_sched_barrier(0);
-        mfmas_ops<C, 2, DMA ? D3 : 0>(acc, af[3], bf[3], af[0], bf[0], nxt, 0, af[1], bf[1], nxt, 1, wm, wn, lane,
-                                      cs, dma_lds, wave, kb, D1 + D2);
+        mfmas_ops<C, MB, 2, D3, NA>(acc, af[3], bf[3], af[0], bf[0], nxt, 0, af[1], bf[1], nxt, 1, wm, wn, lane, cs,
+                                    dma_lds, wave, kb, D1 + D2);
         __builtin_amdgcn_sched_barrier(0);
     };
+    using own = std::integral_constant<int, 2 * MB>;    // the A copies of this tile's height
+    using all = std::integral_constant<int, C::A_DMA>;  // of any tile's
     int kt = 0;
-    for (; kt + 2 < n; ++kt) kstep(kt, std::true_type{}, (ka + kt + 2) * C::BK * 2);
+    const int n_own = n - (tv != 0 ? 3 : 2);
+    for (; kt < n_own; ++kt) kstep(kt, own{}, false, (ka + kt + 2) * C::BK * 2);
+    if constexpr (C::kVar) {
+        if (tv != 0) {
+            dma_tail<C>(src, tv, wave, lane);
+            kstep(kt, own{}, false, (ka + kt + 2) * C::BK * 2);
+            ++kt;
+        }
+    }
     // this item's copies are all issued: the last two K-steps copy K-steps
     // j = kt + 2 - n of the next item; where it has no such K-step (or there
     // is no next item) they copy one it (or this item) has into the free
@@ -691,7 +853,7 @@ __device__ __forceinline__ void tile_ksteps(f32x16 (&acc)[C::NMAT][C::MB][C::NB]
     for (; kt < n; ++kt) {
         const int j = kt + 2 - n;
         const int kj = nn > 0 ? nka + min(j, nn - 1) : ka;
-        kstep(kt, std::true_type{}, kj * C::BK * 2);
+        kstep(kt, all{}, tv != 0 && kt + 2 == n, kj * C::BK * 2);
     }
     // no next item: the last copies (into free slots) complete before the
     // workgroup can end, so none lands in a later workgroup's LDS
@@ -702,12 +864,12 @@ __device__ __forceinline__ void tile_ksteps(f32x16 (&acc)[C::NMAT][C::MB][C::NB]
     if (n == 1 && nn > 0) dma_stage<C>(src, lds0 + ((n + s0) & 1) * C::STAGE, wave, nka * C::BK * 2);
 }
 
-template <class C>
+template <class C, int MB>
 __device__ __forceinline__ void zero_acc(f32x16 (&acc)[C::NMAT][C::MB][C::NB]) {
 #pragma unroll
     for (int mat = 0; mat < C::NMAT; ++mat)
 #pragma unroll
-        for (int mb = 0; mb < C::MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < C::NB; ++nb)
 #pragma unroll
@@ -758,15 +920,15 @@ __device__ __forceinline__ uint4 load_coherent(const uint16_t* p) {
 
 // The wave's 128 rows of one tile, columns [c0, c0 + 128) of y, are written
 // (and complete): count them, and finish the token chunks they complete.
-template <class C>
+template <class C, int MB>
 __device__ __forceinline__ void fold_rows(const GemmParams& p, const TileCoord& tc, int wm, int c0, int lane) {
     const FoldArgs& f = p.fold;
     if (c0 >= p.N) return;  // the wave's columns lie past the row end
     const int k = f.k, chunk = c0 / 128, nchunk = p.N / 128;
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
+    for (int hh = 0; hh < MB / 2; ++hh) {
         const int lr = hh * 64 + lane;  // the wave's local row
-        const int gm = tc.m0 + dma_arow<C>(wm, lr / 32) + lr % 32;
+        const int gm = tc.m0 + dma_arow(wm, 0, MB) + lr;
         bool last = false;
         int t = 0;
         if (gm < tc.m_end) {
@@ -825,7 +987,7 @@ __device__ __forceinline__ void fold_rows(const GemmParams& p, const TileCoord& 
     }
 }
 
-template <class C, bool GATED, bool FOLD = false>
+template <class C, bool GATED, int MB, bool FOLD = false>
 __device__ __forceinline__ void store_tile(const f32x16 (&acc)[C::NMAT][C::MB][C::NB], const GemmParams& p,
                                            const TileCoord& tc, char* smem, int wave, int lane,
                                            char* piece = nullptr) {
@@ -833,7 +995,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[C::NMAT][C::MB][C
     uint16_t* st = (uint16_t*)(smem + C::STG_OFF + wave * C::HSTG);
     const int l32 = lane & 31;
     const int row0 = tc.m0, col0 = tc.n0 + wn * C::WTN;
-    if (piece) {
+    if (MB == C::MB && piece) {  // (split tiles are whole)
         float4* d = (float4*)piece;
 #pragma unroll
         for (int mb = 0; mb < C::MB; ++mb)
@@ -854,8 +1016,8 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[C::NMAT][C::MB][C
         return;
     }
 #pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb) {
-        if (row0 + dma_arow<C>(wm, mb) >= tc.m_end) continue;  // a block wholly past the segment
+    for (int mb = 0; mb < MB; ++mb) {
+        if (row0 + dma_arow(wm, mb, MB) >= tc.m_end) continue;  // a block wholly past the segment
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             // rows 16h .. 16h+15 of the 32-row block: accumulator elements 8h .. 8h+7
@@ -904,7 +1066,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[C::NMAT][C::MB][C
             for (int k = 0; k < 16 * C::CPR / 64; ++k) {
                 const int c = lane + 64 * k;
                 const int rr = c / C::CPR, cc = c % C::CPR;
-                const int gm = row0 + dma_arow<C>(wm, mb) + 16 * h + rr, gn = col0 + cc * 8;
+                const int gm = row0 + dma_arow(wm, mb, MB) + 16 * h + rr, gn = col0 + cc * 8;
                 const uint4 v = *(const uint4*)(st + rr * C::SROW + cc * 8);
                 if (gm < tc.m_end && gn < p.N) {
                     if constexpr (FOLD) store_coherent(p.C + (size_t)gm * p.N + gn, v);
@@ -917,113 +1079,85 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[C::NMAT][C::MB][C
     if constexpr (FOLD) {
         static_assert(!GATED && C::WTN == 128, "the fold works on the down projection's 128-column wave tiles");
         wait_vmcnt<0>();  // this wave's y stores are complete at the coherence point
-        fold_rows<C>(p, tc, wm, col0, lane);
+        fold_rows<C, MB>(p, tc, wm, col0, lane);
     }
 }
 
-// Work of P persistent workgroups: F rounds of one tile each (round r, tile
-// r*P + w; the last round may be partial), then, split by K-steps, the tiles
-// [F*P, total): each workgroup gets `share` consecutive K-steps of those.
-// The split moves two fp32 tile pieces per workgroup through memory and
-// restarts the pipeline per piece, so it is used (with a workspace) only when
-// whole tiles would leave the workgroups idle for more than min_idle K-steps
-// on average (the caller's threshold, kSkMinIdle by default).
-constexpr int kSkMinIdle = 48;
-constexpr int kSkMinShare = 8;  // K-steps: the shortest piece worth a pipeline restart
-struct SkSplit {
-    int F, W, share;
-};
-__device__ __forceinline__ SkSplit sk_split(int total, int nk, int P, bool can_split, int min_idle) {
-    SkSplit k;
-    const int rounds = ceil_div(total, P);
-    const int64_t idle = (int64_t)(rounds * P - total) * nk;  // K-steps, summed over workgroups
-    if (!can_split || total == 0 || idle <= (int64_t)min_idle * P) {
-        k.F = rounds;
-        k.W = 0;
-        k.share = 1;
-    } else {
-        // split only the last partial round when its K-steps still give every
-        // workgroup a piece of kSkMinShare or more (fewer split tiles, fewer
-        // pieces through memory); otherwise the last one to two rounds
-        const int full = total / P;
-        const int64_t rest = (int64_t)(total - full * P) * nk;
-        k.F = rest >= (int64_t)kSkMinShare * P ? full : max(0, full - 1);
-        k.W = (total - k.F * P) * nk;
-        k.share = ceil_div(k.W, P);
-    }
-    return k;
-}
-
-template <bool GATED, bool SK, bool FOLD = false>
+// P = gridDim.x persistent workgroups (a multiple of 8); ws: the stream-K
+// workspace, or nullptr (tiles stay whole).
+template <bool GATED, bool VAR, bool FOLD = false>
 __global__ __launch_bounds__(kGemmThreads, 1) void grouped_gemm_dma_kernel(GemmParams p, char* ws) {
-    using C = DmaCfg<GATED>;
+    using C = DmaCfg<GATED, VAR>;
     __shared__ __align__(16) char smem[C::SMEM];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const TileSched ts = tile_sched(p, smem + C::SCHED_OFF, C::BM, C::BN);
-    const int total = ts.total_mt * ts.NT;
-    const int nk = p.K / C::BK;
-    f32x16 acc[C::NMAT][C::MB][C::NB];
+    const int P = gridDim.x;
+    const int pw = xcd_swizzle(blockIdx.x, P);
+    SkSplit sk;
+    const TileSched ts = tile_sched<C>(p, smem + C::SCHED_OFF, P, ws != nullptr, sk);
+    const int total = ts.total();
+    const int nk = ceil_div(p.K, C::BK);
     DmaSrc<C> src;
-    if constexpr (!SK) {
-        const int L = xcd_swizzle(blockIdx.x, gridDim.x);
-        if (L >= total) return;
-        const TileCoord tc = tile_coord(ts, p.n_seg, L, C::BM, C::BN);
-        dma_sources<C, GATED>(src, p, tc, wave, lane);
-        zero_acc<C>(acc);
-        ksteps_prologue<C>(src, smem, 0, nk, wave);
-        tile_ksteps<C, GATED>(acc, src, smem, 0, nk, wave, lane, kAfterNone, 0, p, tc, 0, 0);
-        store_tile<C, GATED, FOLD>(acc, p, tc, smem, wave, lane);
-    } else {
-        const int P = gridDim.x;
-        const int pw = xcd_swizzle(blockIdx.x, P);
-        const SkSplit sk = sk_split(total, nk, P, ws != nullptr, p.sk_min_idle);
-        // work items: full rounds (one tile each), then this workgroup's share
-        // of the remaining K-steps; one loop so every stage is inlined once
-        const int i0 = min(sk.W, pw * sk.share), i1 = min(sk.W, i0 + sk.share);
-        int r = 0, i = i0;
-        // the next work item (L < 0: none left)
-        auto next_item = [&](int& L, int& ka, int& kb, int& slot) {
-            slot = -1;
-            while (r < sk.F) {
-                L = r * P + pw;
-                ka = 0;
-                kb = nk;
-                ++r;
-                if (L < total) return;  // the last whole-tile round may be partial
-            }
-            if (i < i1) {
-                const int t = i / nk;
-                ka = i - t * nk;
-                kb = min(nk, ka + (i1 - i));
-                L = sk.F * P + t;
-                // slot 0: the piece that starts the share, slot 1: the one that ends it
-                if (ka != 0 || kb != nk) slot = i == i0 ? 0 : 1;
-                i += kb - ka;
-                return;
-            }
-            L = -1;
-        };
-        // The next item's first two K-steps are copied during this item's
-        // last two (tile_ksteps), so they land while this item's results go
-        // out and the pipeline does not drain between items.
-        int L, ka, kb, slot;
-        next_item(L, ka, kb, slot);
-        TileCoord tc;
-        if (L >= 0) {
-            tc = tile_coord(ts, p.n_seg, L, C::BM, C::BN);
-            dma_sources<C, GATED>(src, p, tc, wave, lane);
-            ksteps_prologue<C>(src, smem, ka, kb, wave);
+    // work items: full rounds (one tile each), then this workgroup's share
+    // of the remaining K-steps; one loop so every stage is inlined once
+    const int i0 = min(sk.W, pw * sk.share), i1 = min(sk.W, i0 + sk.share);
+    // in the round after the one with the first half tiles the workgroups
+    // take theirs in the opposite order: those that had a half tile first
+    const int r0 = ts.full_mt * ts.NT / P;
+    // With half tiles, the workgroups of every second XCD take theirs first: a
+    // half tile does half the work per byte of weights, and a round of nothing
+    // else would be bound by HBM (half of the CUs at a time are not).
+    const int rh = r0 + (r0 * P + pw < ts.full_mt * ts.NT ? 1 : 0);  // this workgroup's first round of half tiles
+    const int rot = VAR && ts.half_mt > 0 && (blockIdx.x & 1) ? rh : 0;
+    int r = 0, i = i0;
+    // the next work item (L < 0: none left)
+    auto next_item = [&](int& L, int& ka, int& kb, int& slot) {
+        slot = -1;
+        while (r < sk.F) {
+            const int q = r + rot < sk.F ? r + rot : r + rot - sk.F;
+            L = q * P + (VAR && q > r0 && ((q - r0) & 1) ? P - 1 - pw : pw);
+            ka = 0;
+            kb = nk;
+            ++r;
+            if (L < total) return;  // the last whole-tile round may be partial
         }
-        int after = kAfterNone, s0 = 0;
-        while (L >= 0) {
-            zero_acc<C>(acc);
+        if (i < i1) {
+            const int t = i / nk;
+            ka = i - t * nk;
+            kb = min(nk, ka + (i1 - i));
+            L = sk.F * P + t;
+            // slot 0: the piece that starts the share, slot 1: the one that ends it
+            if (ka != 0 || kb != nk) slot = i == i0 ? 0 : 1;
+            i += kb - ka;
+            return;
+        }
+        L = -1;
+    };
+    // The next item's first two K-steps are copied during this item's
+    // last two (tile_ksteps), so they land while this item's results go
+    // out and the pipeline does not drain between items.
+    int L, ka, kb, slot;
+    next_item(L, ka, kb, slot);
+    TileCoord tc;
+    tc.half = false;
+    if (L >= 0) {
+        tc = tile_coord<C>(ts, p.n_seg, L);
+        dma_sources<C, GATED>(src, p, tc, wave, lane);
+        ksteps_prologue<C>(src, smem, ka, kb, wave);
+    }
+    int after = kAfterNone, s0 = 0;
+    // the work items of one height, while they last
+    auto items = [&](auto blocks) {
+        constexpr int MB = decltype(blocks)::value;
+        while (L >= 0 && (!VAR || tc.half == (MB != C::MB))) {
+            f32x16 acc[C::NMAT][C::MB][C::NB];
+            zero_acc<C, MB>(acc);
             int L2, ka2, kb2, slot2;
             next_item(L2, ka2, kb2, slot2);
             TileCoord tc2 = tc;
-            if (L2 >= 0) tc2 = tile_coord(ts, p.n_seg, L2, C::BM, C::BN);
-            tile_ksteps<C, GATED>(acc, src, smem, ka, kb, wave, lane, after, s0, p, tc2, ka2, L2 >= 0 ? kb2 : ka2);
-            store_tile<C, GATED, FOLD>(acc, p, tc, smem, wave, lane,
-                                       slot < 0 ? nullptr : ws + ((size_t)2 * pw + slot) * kSkSlotBytes);
+            if (L2 >= 0) tc2 = tile_coord<C>(ts, p.n_seg, L2);
+            tile_ksteps<C, GATED, MB>(acc, src, smem, ka, kb, wave, lane, after, s0, p, tc2, ka2, L2 >= 0 ? kb2 : ka2);
+            store_tile<C, GATED, MB, FOLD>(acc, p, tc, smem, wave, lane,
+                                           slot < 0 ? nullptr : ws + ((size_t)2 * pw + slot) * kSkSlotBytes);
             after = kAfterStores;
             s0 = (s0 + kb - ka) & 1;
             L = L2;
@@ -1032,6 +1166,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grouped_gemm_dma_kernel(GemmP
             slot = slot2;
             tc = tc2;
         }
+    };
+    if constexpr (VAR) {
+        while (L >= 0) {
+            items(std::integral_constant<int, C::MB>{});
+            items(std::integral_constant<int, C::MB / 2>{});
+        }
+    } else {
+        items(std::integral_constant<int, C::MB>{});
     }
 }
 
@@ -1070,7 +1212,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_fixup_kernel(GemmParams p, 
     const SkSplit sk = sk_split(total_mt * ceil_div(p.N, C::BN), nk, P, true, p.sk_min_idle);
     const int nsplit = sk.W / nk;  // tiles of the split range
     if (nsplit == 0 || (int)blockIdx.x >= nsplit * kFixSplit) return;
-    const TileSched ts = tile_sched(p, sched, C::BM, C::BN);
+    SkSplit again;
+    const TileSched ts = tile_sched<C>(p, sched, P, true, again);
     constexpr int NQ = C::MB * C::NB * 4;  // float4 slots of one matrix per thread
     static_assert(NQ % kFixSplit == 0, "slices of whole slots");
     constexpr int QPER = NQ / kFixSplit;
@@ -1081,7 +1224,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_fixup_kernel(GemmParams p, 
         const int q = (t * nk / sk.share + 1) * sk.share;
         if (q >= (t + 1) * nk) continue;  // no boundary inside: computed whole
         const int p0 = t * nk / sk.share, p1 = ((t + 1) * nk - 1) / sk.share;
-        const TileCoord tc = tile_coord(ts, p.n_seg, sk.F * P + t, C::BM, C::BN);
+        const TileCoord tc = tile_coord<C>(ts, p.n_seg, sk.F * P + t);
         float4 sum[QPER][C::NMAT];
 #pragma unroll
         for (int k = 0; k < QPER; ++k)
@@ -1128,7 +1271,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_fixup_kernel(GemmParams p, 
         for (int k = 0; k < QPER; ++k) {
             const int qq = qs * QPER + k;  // slot (mb, nb, i4) in the order of store_piece
             const int i4 = qq & 3, nb = (qq >> 2) % C::NB, mb = (qq >> 2) / C::NB;
-            const int r0 = dma_arow<C>(wm, mb) + 8 * i4 + 4 * (lane >> 5);
+            const int r0 = dma_arow(wm, mb, C::MB) + 8 * i4 + 4 * (lane >> 5);  // (split tiles are whole)
             const int gn = tc.n0 + wn * C::WTN + nb * 32 + (lane & 31);
             const float g4[4] = {sum[k][0].x, sum[k][0].y, sum[k][0].z, sum[k][0].w};
             const float4 u = sum[k][C::NMAT - 1];
@@ -1156,6 +1299,18 @@ static int stream_k_workgroups() {
     return cached[dev];
 }
 
+// Whether the kernel with half tiles and ragged K-steps (VAR) runs. Ragged K
+// needs it. Otherwise it saves the padding of the segments' last tiles, half a
+// tile in two on average, so 128 of rows_cap / n_seg rows, and costs 2-3 % of
+// the GEMMs in per-tile scalar work. With 400 rows per segment on average
+// (partial brownout, 3001 tokens) the layer runs 307-322 -> 284-295 us; with
+// 1024 rows and no tails 559 -> 564 us (grouping search), with 2184 rows
+// (fine-shaped) it gains at most 1 %, with 6144 (heavy-shaped) it loses 1 %.
+constexpr int kVarRows = 768;
+static bool gemm_var_pays(const GemmParams& g) {
+    return g.K % kDmaBK != 0 || (int64_t)g.rows_cap < (int64_t)g.n_seg * kVarRows;
+}
+
 template <bool GATED>
 hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipStream_t s) {
     using C = DmaCfg<GATED>;
@@ -1163,36 +1318,33 @@ hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipS
     g.sk_min_idle = g0.sk_min_idle < 0 ? kSkMinIdle : g0.sk_min_idle;
     // persistent: one workgroup per CU, each XCD a contiguous range of tiles
     const int P = stream_k_workgroups();
+    if (P <= 0) return hipErrorInvalidDevice;
     if constexpr (!GATED) {
         if (g.fold.out != nullptr) {
             // the fold needs every tile whole (no stream-K pieces)
-            if (P <= 0) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((grouped_gemm_dma_kernel<false, true, true>), dim3(P), dim3(kGemmThreads), 0, s, g,
+            if (g.K % C::BK != 0) return hipErrorInvalidValue;  // (ffn_can_fold)
+            hipLaunchKernelGGL((grouped_gemm_dma_kernel<false, false, true>), dim3(P), dim3(kGemmThreads), 0, s, g,
                                (char*)nullptr);
             return hipGetLastError();
         }
     }
-    if (P > 0) {
-        // Whole tiles leave at most P - 1 workgroups without one in the last
-        // round, so tiles of at most min_idle K-steps are never split,
-        // whatever the offsets say: no workspace, and no launch of a fixup
-        // with nothing to do (4.7 us in a chain of launches; d or d_ff up to
-        // 48 K-steps: fine layer 564 -> 553 us).
-        const bool can = (int64_t)(P - 1) * (g.K / C::BK) > (int64_t)g.sk_min_idle * P;
-        const bool split = can && ws != nullptr && ws_bytes >= (size_t)2 * P * kSkSlotBytes;
+    // Whole tiles leave at most P - 1 workgroups without one in the last
+    // round, so tiles of at most min_idle K-steps are never split,
+    // whatever the offsets say: no workspace, and no launch of a fixup
+    // with nothing to do (4.7 us in a chain of launches; d or d_ff up to
+    // 48 K-steps: partial-brownout layer of 3001 tokens 315 -> 308 us).
+    // Nor are tiles whose K is not whole K-steps (gemm_dma_fits).
+    const bool can = g.K % C::BK == 0 && (int64_t)(P - 1) * (g.K / C::BK) > (int64_t)g.sk_min_idle * P;
+    const bool split = can && ws != nullptr && ws_bytes >= (size_t)2 * P * kSkSlotBytes;
+    if (gemm_var_pays(g))
         hipLaunchKernelGGL((grouped_gemm_dma_kernel<GATED, true>), dim3(P), dim3(kGemmThreads), 0, s, g,
                            split ? (char*)ws : (char*)nullptr);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess || !split) return e;
-        hipLaunchKernelGGL((gemm_fixup_kernel<GATED>), dim3(P), dim3(kGemmThreads), 0, s, g, (const char*)ws, P);
-        return hipGetLastError();
-    }
-    const int64_t mt_max = ceil_div64(g.rows_cap, C::BM) + g.n_seg;
-    const int64_t nt = ceil_div64(g.N, C::BN);
-    int64_t blocks = (mt_max * nt + 7) / 8 * 8;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((grouped_gemm_dma_kernel<GATED, false>), dim3((unsigned)blocks), dim3(kGemmThreads), 0, s, g,
-                       (char*)nullptr);
+    else
+        hipLaunchKernelGGL((grouped_gemm_dma_kernel<GATED, false>), dim3(P), dim3(kGemmThreads), 0, s, g,
+                           split ? (char*)ws : (char*)nullptr);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !split) return e;
+    hipLaunchKernelGGL((gemm_fixup_kernel<GATED>), dim3(P), dim3(kGemmThreads), 0, s, g, (const char*)ws, P);
     return hipGetLastError();
 }
 
@@ -1203,22 +1355,17 @@ size_t ffn_workspace_bytes() {
     return P > 0 ? (size_t)2 * P * kSkSlotBytes : 0;
 }
 
-// Workgroup tile of the bf16 grouped GEMMs (batches above the skinny
-// kernels' size). When d and d_ff are whole 64-column K-steps, the persistent
-// 256-row kernel with direct-to-LDS copies runs at any group size: from 80
-// rows per group up it measured 1.5-2.4x faster than 128-row register-staged
-// tiles, the padding of each group to whole 256-row tiles included. Otherwise
-// the register-staged kernels: 256-row tiles (128x128 per wave, half the LDS
-// traffic per MFMA) when groups average 1024 rows or more, else 128-row.
-enum { kTile128 = 0, kTile256 = 1, kTileDma = 2 };
-constexpr bool kFdb256 = false;  // no registers left for a second fragment set
-static int ffn_tile(const FfnArgs& a) {
-    if (a.d % kDmaBK == 0 && a.d_ff % kDmaBK == 0) return kTileDma;
-    return (int64_t)a.rows_cap < (int64_t)1024 * a.n_seg ? kTile128 : kTile256;
-}
+// Whether a bf16 GEMM over K columns (above the skinny kernels' batch size)
+// runs on the persistent kernel with direct-to-LDS copies: K of whole 64-column
+// K-steps, or of at least three K-steps with a ragged last one (a shorter ragged
+// K would put the ragged step into the previous tile's copies). It is faster
+// than the register-staged tiles at any group size: 1.5-2.4x from 80 rows per
+// group up (d = 2048, d_ff = 1408); d_ff = 176 (T = 4096, 15 groups, top-4):
+// gate/up 87 -> 68 us, down 74 -> 51 us, layer 200 -> 151 us.
+static bool gemm_dma_fits(int K) { return K % kDmaBK == 0 || K > 2 * kDmaBK; }
 
 bool ffn_can_fold(const FfnArgs& a) {
-    return a.dtype == BMOE_BF16 && a.rows_cap > 0 && !ffn_skinny_fits(a) && ffn_tile(a) == kTileDma &&
+    return a.dtype == BMOE_BF16 && a.rows_cap > 0 && !ffn_skinny_fits(a) && a.d_ff % kDmaBK == 0 && a.d % kDmaBK == 0 &&
            a.d % 128 == 0 && stream_k_workgroups() > 0;
 }
 
@@ -1227,16 +1374,14 @@ hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {
     const bool up = part != 2, down = part != 1;
     if (a.dtype == BMOE_F32) return launch_ffn_f32(a, s, part);
     if (ffn_skinny_fits(a)) return launch_ffn_skinny(a, s, part);
-    const int tile = ffn_tile(a);
     if (up) {
         GemmParams g1{(const uint16_t*)a.a, (const uint16_t*)a.w_gate, (const uint16_t*)a.w_up,
                       (uint16_t*)a.h, a.offsets, a.n_seg, a.rows_cap, a.d_ff, a.d};
         g1.a_rows = a.a_rows;
         g1.a_count = a.a_count;
         g1.sk_min_idle = a.split_min_idle;
-        hipError_t e = tile == kTileDma   ? launch_gemm_dma<true>(g1, a.ws, a.ws_bytes, s)
-                       : tile == kTile256 ? launch_gemm<true, 256, 128, 64, kFdb256>(g1, s)
-                                          : launch_gemm<true, 128, 128, 64, true>(g1, s);
+        hipError_t e = gemm_dma_fits(g1.K) ? launch_gemm_dma<true>(g1, a.ws, a.ws_bytes, s)
+                                           : launch_gemm<true, 128, 128, 64, true>(g1, s);
         if (e != hipSuccess) return e;
     }
     if (down) {
@@ -1244,9 +1389,8 @@ hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {
                       a.offsets, a.n_seg, a.rows_cap, a.d, a.d_ff};
         g2.sk_min_idle = a.split_min_idle;
         g2.fold = a.fold;
-        return tile == kTileDma   ? launch_gemm_dma<false>(g2, a.ws, a.ws_bytes, s)
-               : tile == kTile256 ? launch_gemm<false, 256, 256, 64, kFdb256>(g2, s)
-                                  : launch_gemm<false, 128, 256, 64, true>(g2, s);
+        return gemm_dma_fits(g2.K) ? launch_gemm_dma<false>(g2, a.ws, a.ws_bytes, s)
+                                   : launch_gemm<false, 128, 256, 64, true>(g2, s);
     }
     return hipSuccess;
 }

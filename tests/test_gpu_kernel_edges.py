@@ -88,3 +88,37 @@ def test_f32_route(T, d, E, k):
         assert np.array_equal(got[key].cpu().numpy(), ref[key]), key
     assert_gates(got["topk_w"].cpu().numpy(), ref["topk_w"], "topk_w")
     assert_gates(got["slot_gate"].cpu().numpy(), ref["slot_gate"], "slot_gate")
+
+
+def ffn_workspace():
+    return torch.empty(B.workspace_bytes(B.make_desc(1, 64, 1, 1, 1, 64), B.STAGE_FFN), dtype=torch.uint8, device="cuda")
+
+
+TILE_FFN = [
+    # (segment sizes, rows_cap, d, d_ff, tokens gathered from), above the skinny
+    # kernels' size: tails on either side of half a 256-row tile, segments of a
+    # half tile only, ragged last K-steps of every width (8 to 56 columns,
+    # three K-steps and more) in either GEMM, column remainders
+    ((128, 129, 256, 257, 1, 0, 384, 385), 1600, 320, 192, None),
+    ((128, 127, 512, 1), 800, 136, 176, None),
+    ((300, 64), 400, 184, 200, 150),
+    ((130, 700), 900, 168, 136, None),
+    ((513, 40, 0, 200), 800, 152, 144, 300),
+    ((250, 255, 3), 600, 312, 248, None),
+    # more half tiles than workgroups: 60 segments x 5 column tiles of gate/up
+    (tuple(1 + (37 * i) % 128 for i in range(60)), 5000, 128, 584, None),
+    # whole tiles and half tiles in the same round, half tiles in the next
+    (tuple([256] * 20 + [100] * 30), 8400, 192, 1160, None),
+    # ragged K too short for the copies: the register-staged tiles
+    ((200, 130), 400, 72, 104, None),
+]
+
+
+@pytest.mark.parametrize("stream_k", [False, True], ids=["whole", "stream_k"])
+@pytest.mark.parametrize("sizes,cap,d,f,tokens", TILE_FFN, ids=[f"seg{len(c[0])}-d{c[2]}-f{c[3]}" for c in TILE_FFN])
+def test_ffn_tile_heights_and_ragged_k(sizes, cap, d, f, tokens, stream_k):
+    assert cap > 64 * len(sizes) and sum(sizes) <= cap
+    if stream_k and tokens is not None:
+        check_ffn(sizes, cap, d, f, "bf16", 1, tokens, ffn_workspace())
+    else:
+        check_ffn(sizes, cap, d, f, "bf16", 1, tokens, ffn_workspace() if stream_k else None, 0 if stream_k else None)
