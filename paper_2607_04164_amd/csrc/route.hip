@@ -9,6 +9,9 @@
 //              16x16x32 bf16 MFMA, fp32 accumulate; with KS > 1 the waves
 //              split the d axis and their partial tiles are summed in LDS
 //              in a fixed order;
+//        bf16, E <= 64, d of whole 64-column chunks, T <= 8192: the same
+//              copies, but every wave takes every fourth chunk through a ring
+//              of its own, with no barrier;
 //        bf16, E <= 8, d a multiple of 1024 up to 4096: 16 tokens, the
 //              waves split d; each wave loads its x columns straight into
 //              registers (all at once) and copies its W_router columns into
@@ -46,7 +49,9 @@ static_assert(BMOE_MAX_EXPERTS <= kRouteThreads, "one map entry per thread");
 // d = 1024 * NBAT, NBAT <= 4)
 // MODE_BF16_XD: 32 tokens, 17..64 experts, d = 64 * NU (NU in 8, 16, 32): x
 // straight into registers, W_router alone through an LDS ring
-enum { MODE_LOGITS_IN = 0, MODE_F32 = 1, MODE_BF16 = 2, MODE_BF16_RES = 3, MODE_BF16_XD = 4 };
+// MODE_BF16_WR: every wave has a ring of its own of 64-column chunks of x and
+// W_router (d of whole chunks, E <= 64); KW: slots per wave
+enum { MODE_LOGITS_IN = 0, MODE_F32 = 1, MODE_BF16 = 2, MODE_BF16_RES = 3, MODE_BF16_XD = 4, MODE_BF16_WR = 5 };
 __host__ __device__ constexpr bool mode_bf16(int mode) { return mode >= MODE_BF16; }
 
 // KW of MODE_BF16_XD carries NU (k-steps of 32 columns per wave, low 6 bits)
@@ -55,6 +60,9 @@ __host__ __device__ constexpr int xd_nu(int kw) { return kw & 63; }
 __host__ __device__ constexpr int xd_ns(int kw) { return kw >> 6; }
 constexpr int kXdSlot = 16 * 1024;        // 64 router rows x 2 column halves x 64 columns, bf16
 constexpr int kXdPart = 2 * 16 * 64 * 4;  // partial tiles of the waves of the second half
+
+// bytes of a MODE_BF16_WR slot: 64 columns of the x rows, then of the router rows
+__host__ __device__ constexpr int wr_slot(int tb, int nblk) { return (tb + nblk) * 16 * 128; }
 
 // LDS of the router columns (8 rows of d, four wave areas) and of the
 // partial logit tiles of waves 1..3 (also the fp32 logits')
@@ -101,12 +109,13 @@ __host__ __device__ inline RouteSmem route_smem(int E, int d) {
     s.zstride = e_pad + 1;
     s.zs_bytes = ((size_t)bt * s.zstride * 4 + 15) / 16 * 16;
     s.flag_bytes = 2048;
-    s.cand_bytes = 4 * 2048;
+    s.cand_bytes = MODE == MODE_BF16_WR ? 0 : 4 * 2048;  // (shares the drained rings)
     s.dummy_bytes = (MODE == MODE_BF16 || MODE == MODE_BF16_XD) ? 4 * 1024 : 0;
     s.ring_bytes = 0;
     if constexpr (MODE == MODE_BF16) s.ring_bytes = (size_t)RouteCfg<TB, NBLK, KW>::NSLOT * RouteCfg<TB, NBLK, KW>::SLOT;
     if constexpr (MODE == MODE_F32) s.ring_bytes = kResPartBytes;
     if constexpr (MODE == MODE_BF16_RES) s.ring_bytes = res_w_bytes(d) + kResPartBytes;
+    if constexpr (MODE == MODE_BF16_WR) s.ring_bytes = (size_t)4 * KW * wr_slot(TB, NBLK);
     if constexpr (MODE == MODE_BF16_XD) s.ring_bytes = (size_t)xd_ns(KW) * kXdSlot + kXdPart;
     return s;
 }
@@ -792,6 +801,102 @@ __device__ __forceinline__ void logits_bf16_xd(const RouteArgs& p, float* zs, ch
     }
 }
 
+// Logits of 16 TB tokens for up to 16 NBLK experts, d a multiple of 64, with no
+// barrier in the copy phase: wave w takes the 64-column chunks w, w + 4, .. of d
+// through a ring of NSL slots of its own. A slot holds a chunk of the x rows and
+// then of the router rows (rows past T and E repeat the last one), one 128-byte
+// line per row, its eight 16-byte pieces XOR-swizzled by (row & 7); a wave waits
+// for its own copies only. The four partial tiles are added in wave order.
+// The x tile goes through LDS although it is read once: loads in the MFMA operand
+// layout (16 rows, 16 bytes of each per quarter wave) cost a tag lookup per lane,
+// four times those of whole lines. Bound by HBM while the copies run (8192
+// tokens, d = 2048: 11.5 of the kernel's 27 us, 2.9 TB/s); the selection (6 us)
+// and the float64 decision of a few workgroups (up to 9 us) follow. Kernel trace,
+// d = 2048, 60 experts: 4096 tokens 22.6 us on the x-direct path, 19.2 here; one
+// token 9.6 us on the shared ring, 8.2 here.
+template <int TB, int NBLK, int NSL>
+__device__ __forceinline__ void logits_bf16_wr(const RouteArgs& p, float* zs, char* rings, int t0) {
+    constexpr int BT = 16 * TB, EP = 16 * NBLK, ROWS = BT + EP;
+    constexpr int NDMA = ROWS / 8;  // copy instructions per chunk (8 rows each)
+    constexpr int SLOT = wr_slot(TB, NBLK);
+    static_assert(NSL >= 2 && NSL <= 8 && NDMA * (NSL - 1) <= 63, "copy waits");
+    static_assert(BT * EP * 4 <= NSL * SLOT, "a partial tile fits the wave's ring");
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int q = lane >> 4, r16 = lane & 15;
+    const int d = p.d, E = p.E, T = p.T;
+    char* ring = rings + wave * NSL * SLOT;
+    const uint32_t ring0 = (uint32_t)(uintptr_t)ring;
+    const char* xb = (const char*)p.x + (size_t)t0 * d * 2;
+    const char* wb = (const char*)p.w;
+    uint32_t off[NDMA];
+    const int lrow = lane >> 3, lchk = lane & 7;
+#pragma unroll
+    for (int i = 0; i < NDMA; ++i) {
+        const int r = 8 * i + lrow;  // slot row
+        const int row = i < BT / 8 ? min(r, T - 1 - t0) : min(r - BT, E - 1);
+        off[i] = (uint32_t)row * (uint32_t)d * 2u + (uint32_t)((lchk ^ (r & 7)) << 4);
+    }
+    const int nch = d / 64, mine = nch > wave ? (nch - wave + 3) / 4 : 0;
+    auto issue = [&](int j) {
+        const size_t c = (size_t)(wave + 4 * j) * 128;
+        const uint32_t slot = ring0 + (uint32_t)(j % NSL) * SLOT;
+#pragma unroll
+        for (int i = 0; i < NDMA; ++i) dma16s((i < BT / 8 ? xb : wb) + c, off[i], slot + i * 1024);
+    };
+    f32x4 acc[TB][NBLK];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+        for (int nb = 0; nb < NBLK; ++nb) acc[tb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NSL && j < mine; ++j) issue(j);
+    for (int j = 0; j < mine; ++j) {
+        wait_vmcnt_rt<NDMA>(min(mine - 1 - j, NSL - 1));
+        const char* sl = ring + (j % NSL) * SLOT;
+        uint4 a[2][TB], b[2][NBLK];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const int c = kk * 4 + q;
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) {
+                const int r = tb * 16 + r16;
+                a[kk][tb] = *(const uint4*)(sl + r * 128 + ((c ^ (r & 7)) << 4));
+            }
+#pragma unroll
+            for (int nb = 0; nb < NBLK; ++nb) {
+                const int r = BT + nb * 16 + r16;
+                b[kk][nb] = *(const uint4*)(sl + r * 128 + ((c ^ (r & 7)) << 4));
+            }
+        }
+        // the slot's values are in registers: its next chunk may land
+        lds_reads_done();
+        if (j + NSL < mine) issue(j + NSL);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                for (int nb = 0; nb < NBLK; ++nb) acc[tb][nb] = mfma16(a[kk][tb], b[kk][nb], acc[tb][nb]);
+    }
+    // D[4q + i][r16] of block (tb, nb): token 16 tb + 4q + i, expert 16 nb + r16
+    float* part = (float*)ring;
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+        for (int nb = 0; nb < NBLK; ++nb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[(tb * 16 + 4 * q + i) * EP + nb * 16 + r16] = acc[tb][nb][i];
+    __syncthreads();
+    const float* p0 = (const float*)rings;
+    constexpr int STRIDE = NSL * SLOT / 4;
+    for (int i = tid; i < BT * EP; i += kRouteThreads) {
+        const int tl = i / EP, e = i % EP;
+        if (e < E)
+            zs[tl * (EP + 1) + e] = (p0[i] + p0[STRIDE + i]) + p0[2 * STRIDE + i] + p0[3 * STRIDE + i] +
+                                    (p.bias ? p.bias[e] : 0.f);
+    }
+    __syncthreads();  // the pick areas that follow share the rings
+}
+
 // fp32 logits of 16 tokens on the fp32 MFMA, 16 experts at a time. The four
 // waves split d in units of 16 columns (lane group q takes columns 4q .. 4q+3
 // of a unit with one 16-byte load; MFMA e of the unit multiplies the columns
@@ -885,6 +990,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs p) {
         logits_bf16<TB, NBLK, KW>(p, zs, ring, dummy, t0);
     } else if constexpr (MODE == MODE_BF16_RES) {
         logits_bf16_res<KW>(p, zs, ring, (float*)(ring + res_w_bytes(p.d)), t0);
+    } else if constexpr (MODE == MODE_BF16_WR) {
+        logits_bf16_wr<TB, NBLK, KW>(p, zs, ring, t0);
     } else if constexpr (MODE == MODE_BF16_XD) {
         logits_bf16_xd<xd_nu(KW), xd_ns(KW)>(p, zs, ring, dummy, (float*)(ring + xd_ns(KW) * kXdSlot), t0);
     } else if constexpr (MODE == MODE_F32) {
@@ -1150,20 +1257,35 @@ hipError_t launch_res(const RouteArgs& a, hipStream_t s) {
 }
 
 // x straight into registers, W_router alone through the ring: 17..64 experts,
-// d of 512, 1024 or 2048 columns, at least 4096 tokens (128 workgroups of 32
-// tokens); more than 256 workgroups run two per CU, with three slots each
+// d of 512, 1024 or 2048 columns, more tokens than wr_fits takes (over 256
+// workgroups of 32 tokens: two run per CU, with three slots each)
 bool xd_fits(const RouteArgs& a) {
-    return a.E > 16 && a.E <= 64 && (a.d == 512 || a.d == 1024 || a.d == 2048) && a.T >= 4096;
+    return a.E > 16 && a.E <= 64 && (a.d == 512 || a.d == 1024 || a.d == 2048);
 }
 template <int NU>
 hipError_t launch_xd_nu(const RouteArgs& a, hipStream_t s) {
-    if (ceil_div(a.T, 32) > 256) return launch_one<MODE_BF16_XD, 2, 4, NU + 64 * 3>(a, s);
-    return launch_one<MODE_BF16_XD, 2, 4, NU + 64 * 6>(a, s);
+    return launch_one<MODE_BF16_XD, 2, 4, NU + 64 * 3>(a, s);
 }
 hipError_t launch_xd(const RouteArgs& a, hipStream_t s) {
     if (a.d == 2048) return launch_xd_nu<32>(a, s);
     if (a.d == 1024) return launch_xd_nu<16>(a, s);
     return launch_xd_nu<8>(a, s);
+}
+
+// x and W_router through rings of the waves' own: up to 64 experts, d of whole
+// 64-column chunks, up to 8192 tokens (256 workgroups of 32). More tokens would
+// run two rounds of workgroups (their rings fill a CU's LDS): 12289 tokens, 64
+// experts, d = 2048 take 31.7 us against 27.7 on the x-direct path, whose
+// workgroups run two per CU.
+bool wr_fits(const RouteArgs& a) { return a.d % 64 == 0 && a.E <= 64 && a.T <= 8192; }
+hipError_t launch_wr(const RouteArgs& a, hipStream_t s) {
+    // tiles of 16 tokens while those are one round of workgroups
+    if (a.E <= 16) {
+        if (a.T > 4096) return launch_one<MODE_BF16_WR, 2, 1, 6>(a, s);
+        return launch_one<MODE_BF16_WR, 1, 1, 8>(a, s);
+    }
+    if (a.T > 4096) return launch_one<MODE_BF16_WR, 2, 4, 3>(a, s);
+    return launch_one<MODE_BF16_WR, 1, 4, 3>(a, s);
 }
 
 template <int TB>
@@ -1188,6 +1310,7 @@ hipError_t launch_route(const RouteArgs& a, hipStream_t s) {
     if (a.logits_in) return launch_one<MODE_LOGITS_IN, 1, 1>(a, s);
     if (a.dtype == BMOE_F32) return launch_one<MODE_F32, 1, 1>(a, s);
     if (res_fits(a)) return launch_res(a, s);
+    if (wr_fits(a)) return launch_wr(a, s);
     if (xd_fits(a)) return launch_xd(a, s);
     // tokens per workgroup: as many as keep >= 256 workgroups (one per CU), so
     // that W_router (L2-resident) is re-read as few times as possible

@@ -122,3 +122,51 @@ def test_ffn_tile_heights_and_ragged_k(sizes, cap, d, f, tokens, stream_k):
         check_ffn(sizes, cap, d, f, "bf16", 1, tokens, ffn_workspace())
     else:
         check_ffn(sizes, cap, d, f, "bf16", 1, tokens, ffn_workspace() if stream_k else None, 0 if stream_k else None)
+
+
+SKINNY = [
+    # (segment sizes, spare rows, d, d_ff, tokens gathered from); capacity of at
+    # most 64 rows per segment. Up to 256 workgroups of 64 columns (over the
+    # segments that can have rows) take the register kernel, more the ring kernel
+    ((1,), 0, 8, 8, None),                               # fewer K units than waves, half a column tile
+    ((16, 17, 32, 33, 64, 65, 0), 3, 256, 72, None),     # every row-tile count, two passes
+    ((15, 0, 48, 1), 0, 1032, 40, 30),                   # K = 32 units + 8 columns, gathered
+    (tuple((7 * i) % 5 for i in range(100)), 20, 64, 24, 40),  # more segments than lanes, some empty
+    (tuple(1 + i % 3 for i in range(60)), 40, 320, 328, None),  # ring gate/up (6 x 60), register down (ragged K)
+    (tuple(3 * (i % 4) for i in range(70)), 100, 256, 384, 50),  # ring both, K of 4 and 6 chunks, gathered
+    ((70, 0, 64, 129) + (1,) * 60, 300, 192, 320, None),  # ring: two and three passes
+]
+
+
+@pytest.mark.parametrize("sizes,spare,d,f,tokens", SKINNY, ids=[f"seg{len(c[0])}-d{c[2]}-f{c[3]}" for c in SKINNY])
+def test_skinny_ffn(sizes, spare, d, f, tokens):
+    cap = sum(sizes) + spare
+    assert cap <= 64 * len(sizes)
+    check_ffn(sizes, cap, d, f, "bf16", 2, tokens)
+
+
+ROUTE = [
+    # (experts, d, top_k, tokens): rings of the waves' own with fewer chunks than
+    # waves, more chunks than slots, ragged token tiles of 16 (up to 4096 tokens)
+    # and 32, one and four blocks of experts, picks past the register list; then
+    # both sides of their rules (d not whole chunks, more experts, more tokens)
+    (9, 64, 2, 40), (64, 64, 5, 17), (3, 320, 2, 33), (16, 192, 3, 4130), (40, 576, 9, 4110), (17, 2112, 4, 4096),
+    (60, 2048, 4, 1), (12, 72, 3, 300), (65, 256, 4, 300), (33, 512, 3, 8193), (16, 640, 16, 50),
+]
+
+
+@pytest.mark.parametrize("E,d,k,T", ROUTE, ids=[f"E{c[0]}-d{c[1]}-k{c[2]}-T{c[3]}" for c in ROUTE])
+def test_route_paths(E, d, k, T):
+    cfg = W.LayerConfig("rpath", T=T, d=d, E=E, top_k=k, G=max(1, E // 2), d_ff=64, dtype="bf16", zipf_s=1.0,
+                        norm_topk=k % 2)
+    L = W.make_layer(cfg, 6, with_weights=False)
+    ref = oracle.route(L.f32("x"), L.f32("w_router"), L.bias, L.e2g, k, cfg.norm_topk)
+    got = B.route(desc_of(cfg), dev_tensor(L.x, "bf16"), dev_tensor(L.w_router, "bf16"), torch.from_numpy(L.bias).cuda(),
+                  torch.from_numpy(L.e2g).cuda(), want_logits=True)
+    torch.cuda.synchronize()
+    zerr = np.abs(got["logits"].cpu().numpy().astype(np.float64) - ref["logits"]).max()
+    assert zerr < B.ROUTE_RECHECK_GAP / 4, f"fp32 logit error {zerr:.3e}"
+    for key in ("topk_idx", "slot_group"):
+        assert np.array_equal(got[key].cpu().numpy(), ref[key]), key
+    assert_gates(got["topk_w"].cpu().numpy(), ref["topk_w"], "topk_w")
+    assert_gates(got["slot_gate"].cpu().numpy(), ref["slot_gate"], "slot_gate")
