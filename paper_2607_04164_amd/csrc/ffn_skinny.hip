@@ -1,10 +1,10 @@
 // Skinny grouped GEMMs for decode-sized batches: the per-united-expert
 // SwiGLU FFN of Sec. 2.1 when every group holds only a few dozen rows, so the
-// layer is bound by streaming the united-expert weights, not by MFMA. Two
-// kernels share the grid and the MFMA layout: skinny_dma_kernel (further
-// down) copies every operand straight into LDS and runs whenever K is a
-// multiple of 64; skinny_gemm_kernel, described here, stages operands through
-// registers and takes any K.
+// layer is bound by streaming the united-expert weights, not by MFMA. Three
+// kernels share the MFMA layout: skinny_reg_kernel (last) takes batches of few
+// rows; of the others, skinny_dma_kernel copies every operand straight into
+// LDS and runs whenever K is a multiple of 64; skinny_gemm_kernel, described
+// here, stages operands through registers and takes any K.
 //
 // One workgroup (4 waves) owns one segment and 64 output columns; wave w owns
 // columns n0 .. n0+15 with n0 = 64*cb + 16*w (for the fused gate/up GEMM: those
@@ -373,11 +373,191 @@ __global__ __launch_bounds__(kSkThreads, 1) void skinny_dma_kernel(SkinnyParams 
     }
 }
 
+// ---- few rows: 16-column tiles, K split over the waves
+//
+// The ring kernel's 64-column workgroups (one per CU: the ring fills LDS)
+// leave most of the CUs idle when a batch of a few tokens reaches a handful of
+// segments (one token, top-4, d_ff = 1408: 88 workgroups for gate/up), and
+// copy 64 activation rows whatever the segment holds. Here a workgroup owns 16
+// columns and its four waves split K: wave w takes the 64-column pairs of MFMA
+// steps (whole 128-byte lines) w, w + 4, .. of the weight rows straight into
+// registers in the MFMA layout. Bound by the latency of the loads, so PAIRS
+// pairs per wave are in flight at once, with the activations of the first 16
+// rows; further row tiles reuse the weights. The partial tiles are added
+// through LDS in wave order. Weights cold, d = 2048, d_ff = 1408, top-4, in us,
+// ring -> this kernel: 1 token gate/up 15.5 -> 12.4, down 9.0 -> 8.0; 12 tokens
+// (15 groups) 39.4 -> 32.2, 17.0 -> 14.5; d_ff = 176, 4 tokens 15.1 -> 7.4,
+// 9.3 -> 3.9.
+constexpr int kRgCols = 16;  // output columns per workgroup
+
+// Pairs in flight per wave: gate/up the eight that 256 registers hold (all of
+// K = 2048; six and four measured the same or slower up to d = 2048); down
+// four, which leave room for five workgroups per CU (d_ff = 14336, 1 token:
+// 34.9 us, 51 with six or eight), or six where those are all of K and four are
+// not (d_ff = 1408, 1 token: 9.0 -> 8.0 us).
+// Row tiles per pass: four for gate/up; two for down, whose accumulators of
+// four measured slower at every size.
+template <bool GATED, int PAIRS>
+__global__ __launch_bounds__(kSkThreads, 2) void skinny_reg_kernel(SkinnyParams p) {
+    constexpr int NMAT = GATED ? 2 : 1;
+    constexpr int U = 2 * PAIRS;  // MFMA steps of 32 columns
+    constexpr int TILES = GATED ? 4 : 2;
+    __shared__ __align__(16) f32x4 part[4][NMAT * TILES][64];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int K = p.K, N = p.N;
+    const int ncb = ceil_div(N, kRgCols);
+    const int s = blockIdx.x / ncb, cb = blockIdx.x % ncb;
+    if (s >= p.n_seg) return;
+    const int beg = min(max(p.offsets[s], 0), p.rows_cap);
+    const int end = min(max(p.offsets[s + 1], beg), p.rows_cap);
+    if (end <= beg) return;
+    const int npairs = K / 64;
+    const int r16 = lane & 15, q = lane >> 4;
+    const int n0 = cb * kRgCols;
+    const int wrow = min(n0 + r16, N - 1);  // clamped: loads stay in bounds
+    const uint16_t* wp[NMAT];
+    wp[0] = p.B0 + ((size_t)s * N + wrow) * K + q * 8;
+    if constexpr (GATED) wp[NMAT - 1] = p.B1 + ((size_t)s * N + wrow) * K + q * 8;
+
+    for (int m0 = beg; m0 < end; m0 += 16 * TILES) {
+        const int tiles = min(ceil_div(end - m0, 16), TILES);
+        const uint16_t* xp[TILES];
+#pragma unroll
+        for (int nt = 0; nt < TILES; ++nt)
+            xp[nt] = p.A + (size_t)gathered_row(p.a_rows, p.a_count, min(m0 + nt * 16 + r16, end - 1)) * K + q * 8;
+        f32x4 acc[NMAT][TILES];
+#pragma unroll
+        for (int mat = 0; mat < NMAT; ++mat)
+#pragma unroll
+            for (int nt = 0; nt < TILES; ++nt) acc[mat][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        auto mfmas = [&](int nt, const v4u(&w)[NMAT], v4u x) {
+#pragma unroll
+            for (int mat = 0; mat < NMAT; ++mat)
+                acc[mat][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, w[mat]), __builtin_bit_cast(bf16x8, x), acc[mat][nt], 0, 0, 0);
+        };
+        // step u of the batch from pair p0: columns 32 (u & 1) .. of pair p0 + 4 (u / 2)
+        for (int p0 = wave; p0 < npairs; p0 += 4 * PAIRS) {
+            v4u xv[U], wv[U][NMAT];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (p0 + 4 * (u >> 1) < npairs)
+                    xv[u] = *(const v4u*)(xp[0] + p0 * 64 + (u >> 1) * 256 + (u & 1) * 32);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (p0 + 4 * (u >> 1) < npairs) {
+#pragma unroll
+                    for (int mat = 0; mat < NMAT; ++mat)
+                        wv[u][mat] = *(const v4u*)(wp[mat] + p0 * 64 + (u >> 1) * 256 + (u & 1) * 32);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int nt = 0; nt < TILES; ++nt) {
+                if (nt >= tiles) break;
+                if (nt > 0) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (p0 + 4 * (u >> 1) < npairs)
+                            xv[u] = *(const v4u*)(xp[nt] + p0 * 64 + (u >> 1) * 256 + (u & 1) * 32);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (p0 + 4 * (u >> 1) < npairs) mfmas(nt, wv[u], xv[u]);
+            }
+        }
+        // the columns past the last whole pair: zeros in both operands past K
+        if (K % 64 && wave == (npairs & 3)) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int col = npairs * 64 + u * 32;
+                const bool in = col + q * 8 < K;
+                v4u wt[NMAT];
+#pragma unroll
+                for (int mat = 0; mat < NMAT; ++mat) wt[mat] = in ? *(const v4u*)(wp[mat] + col) : v4u{0, 0, 0, 0};
+#pragma unroll
+                for (int nt = 0; nt < TILES; ++nt)
+                    if (nt < tiles) mfmas(nt, wt, in ? *(const v4u*)(xp[nt] + col) : v4u{0, 0, 0, 0});
+            }
+        }
+#pragma unroll
+        for (int nt = 0; nt < TILES; ++nt)
+            if (nt < tiles) {
+#pragma unroll
+                for (int mat = 0; mat < NMAT; ++mat) part[wave][mat * TILES + nt][lane] = acc[mat][nt];
+            }
+        __syncthreads();
+        // wave nt < TILES finishes row tile nt: the lane holds D[weight row 4q+i][segment row r16]
+        const int row = m0 + wave * 16 + r16, col = n0 + 4 * q;
+        if (wave < TILES && row < end) {
+            f32x4 sum[NMAT];
+#pragma unroll
+            for (int mat = 0; mat < NMAT; ++mat) {
+                sum[mat] = part[0][mat * TILES + wave][lane];
+#pragma unroll
+                for (int w = 1; w < 4; ++w) sum[mat] += part[w][mat * TILES + wave][lane];
+            }
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (GATED) v[i] = silu_mul(sum[0][i], sum[NMAT - 1][i]);
+                else v[i] = sum[0][i];
+            }
+            uint16_t* dst = p.C + (size_t)row * N + col;
+            if (col + 3 < N) {
+                *(uint2*)dst = make_uint2(pack_bf16x2_hw(v[0], v[1]), pack_bf16x2_hw(v[2], v[3]));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (col + i < N) dst[i] = f32_to_bf16(v[i]);
+            }
+        }
+        __syncthreads();  // the partials are rewritten by the next pass
+    }
+}
+
+// Whether the 16-column kernel takes a GEMM. What decides is how many of the
+// segments have rows, which the host does not know; it knows that at most
+// min(n_seg, rows_cap) do, hence at most `wide` ring workgroups have work.
+// Sides measured with cold weights (us, ring / this kernel), E = 60 and 8,
+// routed rows of a Zipf law:
+//  - few rows and few workgroups: 1-2 tokens of top-4 or top-6, d_ff = 1408
+//    15.5-15.8 / 11.6-13.6; 4 tokens, 15 groups, d_ff = 704 16.2 / 13.5 and
+//    1408 18.1 / 20.8; down 8.8-9.2 / 6.5-8.4, d_ff = 14336 62 / 36;
+//  - gate/up of so few columns that the ring kernel never fills a fifth of the
+//    CUs: d_ff = 176, 16 tokens 15.2 / 8.4, 60 tokens 15.4 / 13.5;
+//  - a second round of the ring kernel that is nearly empty (most segments
+//    reached, each by a few rows): gate/up of 15 x 22 workgroups, 8 tokens
+//    26.0 / 27.2, 12 tokens 39.4 / 32.2, 32 tokens 42.9 / 37.2, 64 tokens 45 / 45;
+//    down of 15 x 32, 4 tokens 10.5 / 10.5, 8 tokens 16.7 / 12.2, 24 tokens
+//    17.5 / 16.6, 32 tokens 18.3 / 19.2;
+//  - short K that is not whole chunks, which the ring kernel does not take:
+//    down at d_ff = 176 and 352, 4 tokens 9.4 / 3.9-5.0, 60 tokens 10-11 / 6.8-8.8.
+template <bool GATED>
+bool takes_reg(const SkinnyParams& p) {
+    const int64_t rows = p.rows_cap, wide = (int64_t)min(p.n_seg, p.rows_cap) * ceil_div(p.N, kSkCols);
+    if (rows > 16 * (int64_t)p.n_seg) return false;
+    if (rows * wide <= 3072) return true;
+    if (GATED) return wide <= 48 || (wide > 256 && wide <= 512 && rows >= 40 && rows <= 128);
+    return (wide > 256 && rows >= 24 && rows <= 96) || (p.K % kS2KC && p.K <= 512);
+}
+
+template <bool GATED, int PAIRS>
+void launch_reg(const SkinnyParams& sp, int64_t blocks, hipStream_t s) {
+    hipLaunchKernelGGL((skinny_reg_kernel<GATED, PAIRS>), dim3((unsigned)blocks), dim3(kSkThreads), 0, s, sp);
+}
+
 template <bool GATED>
 hipError_t launch_skinny(const SkinnyParams& sp, hipStream_t s) {
     const int64_t blocks = (int64_t)sp.n_seg * ceil_div(sp.N, kSkCols);
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const int64_t narrow = (int64_t)sp.n_seg * ceil_div(sp.N, kRgCols);
+    if (takes_reg<GATED>(sp) && narrow <= 0x7fffffff) {
+        if constexpr (GATED) launch_reg<GATED, 8>(sp, narrow, s);
+        else if (sp.K > 4 * 4 * 64 && sp.K <= 6 * 4 * 64) launch_reg<GATED, 6>(sp, narrow, s);
+        else launch_reg<GATED, 4>(sp, narrow, s);
+        return hipGetLastError();
+    }
     // the copies address A rows by 32-bit byte offsets from A
     const int64_t a_rows = sp.a_rows ? sp.a_count : sp.rows_cap;
     if (sp.K % kS2KC == 0 && a_rows * sp.K * 2 < ((int64_t)1 << 31) && (int64_t)kSkCols * sp.K * 2 < ((int64_t)1 << 31))
