@@ -524,7 +524,11 @@ struct TileSched {
 
 struct TileCoord {
     int s, m0, m_end, n0;
-    bool half;  // 128 rows instead of 256
+    // 128 rows instead of 256. An int: the padding bytes after a bool kept the
+    // compiler from holding the copies of a TileCoord in registers (it put them
+    // in LDS, and every launch took 7-10 us longer: one round of gate/up tiles,
+    // d = 2048, 62 -> 52 us; down 45 -> 38 us)
+    int half;
 };
 
 // Inclusive scan over the 256 threads of a workgroup (total: the sum). buf: 4
@@ -647,7 +651,7 @@ __device__ __forceinline__ TileCoord tile_coord(const TileSched& t, int n_seg, i
         c.m_end = __builtin_amdgcn_readfirstlane(t.s_end[c.s]);
         c.m0 = beg + (c.m_end - beg) / BM * BM;
         c.n0 = (j - i * NT) * BN;
-        c.half = true;
+        c.half = 1;
         return c;
     }
     int lo = 0, hi = n_seg - 1;
@@ -665,7 +669,7 @@ __device__ __forceinline__ TileCoord tile_coord(const TileSched& t, int n_seg, i
     c.m0 = __builtin_amdgcn_readfirstlane(t.s_beg[c.s]) + mt * BM;
     c.m_end = __builtin_amdgcn_readfirstlane(t.s_end[c.s]);
     c.n0 = nt * BN;
-    c.half = false;
+    c.half = 0;
     return c;
 }
 
@@ -1138,7 +1142,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grouped_gemm_dma_kernel(GemmP
     int L, ka, kb, slot;
     next_item(L, ka, kb, slot);
     TileCoord tc;
-    tc.half = false;
+    tc.half = 0;
     if (L >= 0) {
         tc = tile_coord<C>(ts, p.n_seg, L);
         dma_sources<C, GATED>(src, p, tc, wave, lane);
@@ -1148,7 +1152,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grouped_gemm_dma_kernel(GemmP
     // the work items of one height, while they last
     auto items = [&](auto blocks) {
         constexpr int MB = decltype(blocks)::value;
-        while (L >= 0 && (!VAR || tc.half == (MB != C::MB))) {
+        while (L >= 0 && (!VAR || (tc.half != 0) == (MB != C::MB))) {
             f32x16 acc[C::NMAT][C::MB][C::NB];
             zero_acc<C, MB>(acc);
             int L2, ka2, kb2, slot2;
@@ -1303,7 +1307,7 @@ static int stream_k_workgroups() {
 // needs it. Otherwise it saves the padding of the segments' last tiles, half a
 // tile in two on average, so 128 of rows_cap / n_seg rows, and costs 2-3 % of
 // the GEMMs in per-tile scalar work. With 400 rows per segment on average
-// (partial brownout, 3001 tokens) the layer runs 307-322 -> 284-295 us; with
+// (partial brownout, 3001 tokens) the layer runs 307-313 -> 285 us; with
 // 1024 rows and no tails 559 -> 564 us (grouping search), with 2184 rows
 // (fine-shaped) it gains at most 1 %, with 6144 (heavy-shaped) it loses 1 %.
 constexpr int kVarRows = 768;
@@ -1361,7 +1365,7 @@ size_t ffn_workspace_bytes() {
 // K would put the ragged step into the previous tile's copies). It is faster
 // than the register-staged tiles at any group size: 1.5-2.4x from 80 rows per
 // group up (d = 2048, d_ff = 1408); d_ff = 176 (T = 4096, 15 groups, top-4):
-// gate/up 87 -> 68 us, down 74 -> 51 us, layer 200 -> 151 us.
+// layer 200 -> 131 us.
 static bool gemm_dma_fits(int K) { return K % kDmaBK == 0 || K > 2 * kDmaBK; }
 
 bool ffn_can_fold(const FfnArgs& a) {
