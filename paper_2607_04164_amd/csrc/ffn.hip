@@ -716,7 +716,8 @@ __device__ __forceinline__ void dma_sources(DmaSrc<C>& src, const GemmParams& p,
 // Columns of the last K-step when K is not whole K-steps (else 0). The copies
 // of that K-step repeat its first chunk in place of the chunks past the row's
 // end (which may be past the tensor's), and once they have landed the
-// workgroup zeroes the A rows' (tail_zero), so their products vanish.
+// workgroup zeroes them in both operands (tail_zero), so their products vanish
+// (zeros in A alone would make NaN of an infinite weight in the first chunk).
 template <class C>
 __device__ __forceinline__ int tail_cols(const GemmParams& p) { return C::kVar ? p.K % C::BK : 0; }
 
@@ -737,12 +738,16 @@ __device__ __forceinline__ void dma_tail(DmaSrc<C>& src, int tv, int wave, int l
     }
 }
 
-// Zeros the chunks past the tv columns of the last K-step in the A rows of
-// its ring slot (all copies landed); ends with a barrier.
+// Zeros the chunks past the tv columns of the last K-step in the A and B rows
+// of its ring slot (all copies landed); ends with a barrier.
 template <class C>
 __device__ __forceinline__ void tail_zero(char* stage, int tv) {
-    static_assert(C::BM == kGemmThreads, "one row per thread");
-    for (int c = tv / 8; c < C::KC; ++c) *(uint4*)(stage + lds_off<C>(threadIdx.x, c)) = make_uint4(0, 0, 0, 0);
+    static_assert(C::BM == kGemmThreads && C::RB == kGemmThreads, "one row of each operand per thread");
+    for (int c = tv / 8; c < C::KC; ++c) {
+        char* at = stage + lds_off<C>(threadIdx.x, c);
+        *(uint4*)at = make_uint4(0, 0, 0, 0);
+        *(uint4*)(at + C::A_STAGE) = make_uint4(0, 0, 0, 0);
+    }
     lds_reads_done();  // (LDS writes too)
     wg_barrier();
 }

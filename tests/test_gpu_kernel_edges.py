@@ -124,6 +124,41 @@ def test_ffn_tile_heights_and_ragged_k(sizes, cap, d, f, tokens, stream_k):
         check_ffn(sizes, cap, d, f, "bf16", 1, tokens, ffn_workspace() if stream_k else None, 0 if stream_k else None)
 
 
+@pytest.mark.parametrize("part,K,rows", [("up", 200, 150), ("up", 152, 700), ("down", 176, 150), ("down", 312, 700),
+                                         ("up", 72, 150), ("down", 120, 150), ("up", 328, 10), ("down", 72, 10)])
+def test_ffn_infinite_weights_ragged_k(part, K, rows):
+    """An infinite weight in the last 64-column step of a ragged K: the step's
+    padding must not turn it into NaN (0 * inf). Exact inputs (one-hot rows and
+    small integers), so the expected sums are exact."""
+    N, n = 136, 2
+    r = np.random.default_rng(K)
+    # (two segments; the skinny kernels' capacity ends at 64 rows per segment)
+    offsets = torch.tensor([0, rows, 2 * rows], dtype=torch.int32, device="cuda")
+    a = torch.from_numpy(r.integers(1, 4, (2 * rows, K)).astype(np.float32))
+    w = torch.from_numpy(r.integers(-2, 3, (n, N, K)).astype(np.float32))
+    tail = K // 64 * 64
+    w[0, 3, tail + 1], w[1, 5, tail], w[0, 130, K - 1] = float("inf"), float("-inf"), float("inf")
+    want = torch.cat([a[s * rows:(s + 1) * rows].double() @ w[s].double().t() for s in range(n)])
+    ab, wb = a.bfloat16().cuda(), w.bfloat16().cuda()
+    if part == "down":
+        got = B.ffn_down(offsets, ab, wb)
+    else:
+        # gate columns of 64 so that silu is the identity: h = 64 * up
+        gate = torch.zeros_like(w)
+        gate[:, :, 0] = 64.0
+        one = a.clone()
+        one[:, 0] = 1.0
+        want = 64.0 * torch.cat([one[s * rows:(s + 1) * rows].double() @ w[s].double().t() for s in range(n)])
+        got = B.ffn_gate_up(offsets, one.bfloat16().cuda(), gate.bfloat16().cuda(), wb)
+    torch.cuda.synchronize()
+    got = got.double().cpu()
+    inf = want.isinf()
+    assert int(inf.sum()) == 3 * rows
+    assert torch.equal(got[inf], want[inf])
+    # finite sums are whole numbers below 2^24, rounded once to bf16
+    assert torch.equal(got[~inf], want[~inf].float().bfloat16().double())
+
+
 _FEW30 = tuple(1 + i % 5 for i in range(30))
 
 SKINNY = [
