@@ -1295,7 +1295,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_fixup_kernel(GemmParams p, 
     }
 }
 
-// CUs of the current device, rounded down to a multiple of 8 (XCD deal)
+// CUs of the current device, rounded down to a multiple of 8 (XCD deal); 0
+// where the runtime does not say
 static int stream_k_workgroups() {
     static int cached[64] = {0};
     int dev = 0;
@@ -1320,18 +1321,22 @@ static bool gemm_var_pays(const GemmParams& g) {
     return g.K % kDmaBK != 0 || (int64_t)g.rows_cap < (int64_t)g.n_seg * kVarRows;
 }
 
+constexpr int kGemmDefaultP = 256;
+
 template <bool GATED>
 hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipStream_t s) {
     using C = DmaCfg<GATED>;
     GemmParams g = g0;
     g.sk_min_idle = g0.sk_min_idle < 0 ? kSkMinIdle : g0.sk_min_idle;
-    // persistent: one workgroup per CU, each XCD a contiguous range of tiles
-    const int P = stream_k_workgroups();
-    if (P <= 0) return hipErrorInvalidDevice;
+    // persistent: one workgroup per CU, each XCD a contiguous range of tiles.
+    // Any multiple of 8 computes the same, so a device of unknown CU count gets
+    // the chip's, without the split (whose workspace has the device's size).
+    const int cus = stream_k_workgroups();
+    const int P = cus > 0 ? cus : kGemmDefaultP;
     if constexpr (!GATED) {
         if (g.fold.out != nullptr) {
             // the fold needs every tile whole (no stream-K pieces)
-            if (g.K % C::BK != 0) return hipErrorInvalidValue;  // (ffn_can_fold)
+            if (g.K % C::BK != 0 || cus <= 0) return hipErrorInvalidValue;  // (ffn_can_fold)
             hipLaunchKernelGGL((grouped_gemm_dma_kernel<false, false, true>), dim3(P), dim3(kGemmThreads), 0, s, g,
                                (char*)nullptr);
             return hipGetLastError();
@@ -1344,7 +1349,7 @@ hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipS
     // 48 K-steps: partial-brownout layer of 3001 tokens 315 -> 308 us).
     // Nor are tiles whose K is not whole K-steps (gemm_dma_fits).
     const bool can = g.K % C::BK == 0 && (int64_t)(P - 1) * (g.K / C::BK) > (int64_t)g.sk_min_idle * P;
-    const bool split = can && ws != nullptr && ws_bytes >= (size_t)2 * P * kSkSlotBytes;
+    const bool split = can && cus > 0 && ws != nullptr && ws_bytes >= (size_t)2 * P * kSkSlotBytes;
     if (gemm_var_pays(g))
         hipLaunchKernelGGL((grouped_gemm_dma_kernel<GATED, true>), dim3(P), dim3(kGemmThreads), 0, s, g,
                            split ? (char*)ws : (char*)nullptr);
