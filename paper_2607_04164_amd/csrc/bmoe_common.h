@@ -228,6 +228,9 @@ __device__ __forceinline__ int gathered_row(const int32_t* a_rows, int a_count, 
     if (!a_rows) return r;
     return min(max(a_rows[r], 0), a_count - 1);
 }
+// workgroups of a grid of one per CU: the current device's CUs, rounded down to
+// a multiple of 8 (256 where the runtime does not say)
+int persistent_workgroups();
 // bytes of the stream-K workspace on the current device
 size_t ffn_workspace_bytes();
 // part: 0 = both GEMMs, 1 = gate/up only, 2 = down only

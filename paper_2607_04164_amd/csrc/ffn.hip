@@ -1321,8 +1321,6 @@ static bool gemm_var_pays(const GemmParams& g) {
     return g.K % kDmaBK != 0 || (int64_t)g.rows_cap < (int64_t)g.n_seg * kVarRows;
 }
 
-constexpr int kGemmDefaultP = 256;
-
 template <bool GATED>
 hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipStream_t s) {
     using C = DmaCfg<GATED>;
@@ -1332,7 +1330,7 @@ hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipS
     // Any multiple of 8 computes the same, so a device of unknown CU count gets
     // the chip's, without the split (whose workspace has the device's size).
     const int cus = stream_k_workgroups();
-    const int P = cus > 0 ? cus : kGemmDefaultP;
+    const int P = persistent_workgroups();
     if constexpr (!GATED) {
         if (g.fold.out != nullptr) {
             // the fold needs every tile whole (no stream-K pieces)
@@ -1363,6 +1361,11 @@ hipError_t launch_gemm_dma(const GemmParams& g0, void* ws, size_t ws_bytes, hipS
 }
 
 }  // namespace
+
+int persistent_workgroups() {
+    const int cus = stream_k_workgroups();
+    return cus > 0 ? cus : 256;
+}
 
 size_t ffn_workspace_bytes() {
     const int P = stream_k_workgroups();

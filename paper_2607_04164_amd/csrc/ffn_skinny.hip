@@ -22,6 +22,8 @@
 // registers and LDS; the loop is unrolled by two so that no register array is
 // indexed at run time, and chunks past the end hold zero activations instead
 // of branching around MFMAs.
+#include <math.h>
+
 #include "bmoe_common.h"
 
 namespace bmoe {
@@ -516,29 +518,68 @@ __global__ __launch_bounds__(kSkThreads, 2) void skinny_reg_kernel(SkinnyParams 
 }
 
 // Whether the 16-column kernel takes a GEMM. What decides is how many of the
-// segments have rows, which the host does not know; it knows that at most
-// min(n_seg, rows_cap) do, hence at most `wide` ring workgroups have work.
-// Sides measured with cold weights (us, ring / this kernel), E = 60 and 8,
-// routed rows of a Zipf law:
-//  - few rows and few workgroups: 1-2 tokens of top-4 or top-6, d_ff = 1408
-//    15.5-15.8 / 11.6-13.6; 4 tokens, 15 groups, d_ff = 704 16.2 / 13.5 and
-//    1408 18.1 / 20.8; down 8.8-9.2 / 6.5-8.4, d_ff = 14336 62 / 36;
-//  - gate/up of so few columns that the ring kernel never fills a fifth of the
-//    CUs: d_ff = 176, 16 tokens 15.2 / 8.4, 60 tokens 15.4 / 13.5;
-//  - a second round of the ring kernel that is nearly empty (most segments
-//    reached, each by a few rows): gate/up of 15 x 22 workgroups, 8 tokens
-//    26.0 / 27.2, 12 tokens 39.4 / 32.2, 32 tokens 42.9 / 37.2, 64 tokens 45 / 45;
-//    down of 15 x 32, 4 tokens 10.5 / 10.5, 8 tokens 16.7 / 12.2, 24 tokens
-//    17.5 / 16.6, 32 tokens 18.3 / 19.2;
+// ring kernel's workgroups (one per CU) have work, hence how many segments the
+// rows reach. The host does not know the offsets, so it estimates: rows spread
+// evenly reach about n r / (n + r) of n segments, rows that follow a Zipf law
+// over many experts about 2.2 sqrt(r) (10 routing draws each of 60 and 64
+// experts, 4 to 128 rows, s = 1.2: 4.0, 6.4, 8.8, 11.3, 13.3, 15.1, 17.1
+// segments for 4, 8, 16, 32, 48, 64, 96 rows). busy: that times the column
+// workgroups of a segment. Sides below in us, ring / this kernel, weights cold,
+// means of 10 routing draws, d = 2048 and d_ff = 1408 where not given.
+//  gate/up:
+//  - under 0.45 of the CUs busy: 4 rows, 15 segments 16.3 / 13.5; 8 rows 17.0 /
+//    16.4; d_ff = 704, 24 rows 17.2 / 14.9; d = 4096, d_ff = 3584, 2 rows 29.5 /
+//    24.8; one segment (a shared expert), d_ff = 2816, 1 to 16 rows 0.54-0.60 of
+//    the ring kernel's time. Above, the ring kernel is already near the stream
+//    rate: 60 segments, 8 rows 17.8 / 19.3; d = 4096, d_ff = 1792, 12 rows 31.9 /
+//    33.1. K of fewer than 512 whole columns gives the waves too little to load (60
+//    segments, d = d_ff = 256, 48 rows 1.1 of the ring kernel's time); ragged K
+//    competes with the slower register-staged kernel;
+//  - the ring kernel's second round of workgroups, as long as it is under half
+//    full: 15 segments, 64 rows 31.7 / 29.9, 96 rows 39.0 / 32.5; d = 4096,
+//    d_ff = 3584, 16 rows 74.7 / 68.1, but 96 rows 90.4 / 98.2;
+//  - so few columns that the ring kernel never fills a quarter of the CUs: d_ff =
+//    176, 16 rows 15.2 / 8.4, 240 rows 15.4 / 13.5.
+//  down:
+//  - up to 32 rows (a segment then takes one pass, whatever the routing) in one
+//    ring round, 15 segments, 4 rows 9.7 / 8.4, 16 rows 11.5 / 10.7. With K past
+//    the pairs in flight up to three quarters of that round: d = 4096, d_ff =
+//    14336, 4 segments, 6 rows 81.6 / 70.3, 12 rows 92.5 / 83.1; 0.55 where most
+//    segments are empty (their workgroups come and go between the others): 8
+//    segments, 2 rows 66.7 / 61.6, 4 rows 75.0 / 84.9, d_ff = 3584, 6 rows 21.7 /
+//    22.7. One and two segments, d_ff = 2816 0.49-0.61 of the ring kernel's time;
+//  - past one ring round while segments hold few rows: 15 segments, 48 rows
+//    17.6 / 13.3, 96 rows 17.9 / 16.3, but 160 rows 18.4 / 21.0; with K past the
+//    pairs in flight fewer: d = 4096, d_ff = 14336, 8 segments, 16 rows 158.7 /
+//    136.7, 48 rows 173.7 / 179.7, d_ff = 3584, 96 rows 44.7 / 59.1;
 //  - short K that is not whole chunks, which the ring kernel does not take:
-//    down at d_ff = 176 and 352, 4 tokens 9.4 / 3.9-5.0, 60 tokens 10-11 / 6.8-8.8.
+//    d_ff = 176 and 352, 16 rows 9.4 / 3.9-5.0, 240 rows 10-11 / 6.8-8.8.
+// The rule counts on a spread. All rows in one segment (no routing of several
+// picks does that) cost two passes from 33 rows on: 64 rows in one of 15 segments
+// 8.9 / 11.9, of 60 segments 9.5 / 16.4; up to 32 rows 8.7 / 7.2 and 9.3 / 9.1.
 template <bool GATED>
 bool takes_reg(const SkinnyParams& p) {
-    const int64_t rows = p.rows_cap, wide = (int64_t)min(p.n_seg, p.rows_cap) * ceil_div(p.N, kSkCols);
-    if (rows > 16 * (int64_t)p.n_seg) return false;
-    if (rows * wide <= 3072) return true;
-    if (GATED) return wide <= 48 || (wide > 256 && wide <= 512 && rows >= 40 && rows <= 128);
-    return (wide > 256 && rows >= 24 && rows <= 96) || (p.K % kS2KC && p.K <= 512);
+    const int64_t n = p.n_seg, rows = p.rows_cap, cols = ceil_div(p.N, kSkCols);
+    if (rows > 16 * n) return false;
+    const double cus = persistent_workgroups();
+    const double reach = fmin((double)(n * rows) / (double)(n + rows), 2.2 * sqrt((double)rows));
+    const double busy = reach * (double)cols;
+    const int64_t most = (n < rows ? n : rows) * cols;  // ring workgroups with work, at most
+    if (GATED) {
+        if ((double)most <= 0.25 * cus) return true;
+        if (rows > 128) return false;
+        // (from two rows per segment on, as if all of them had rows)
+        const double few = rows < 2 * n ? 0.45 : (double)most <= 0.5 * cus ? 0.45 : 0.0;
+        const bool long_k = p.K >= 512 || p.K % kS2KC;
+        return (long_k && rows <= (n > 6 ? 8 * n : 48) && busy <= few * cus) ||
+               (busy > cus && busy <= 1.45 * cus && (double)most <= 2.0 * cus);
+    }
+    if (p.K % kS2KC && p.K <= 512) return true;
+    const bool in_flight = p.K <= 6 * 4 * 64;  // all of K (launch_skinny)
+    if (busy <= cus)
+        return rows <= 32 && (rows <= 3 * n || busy <= 0.5 * cus) &&
+               (in_flight || busy <= (2.0 * reach >= (double)n ? 0.75 : 0.55) * cus);
+    return rows <= 96 && rows <= (in_flight ? 7 : 4) * n;
 }
 
 template <bool GATED, int PAIRS>

@@ -163,19 +163,21 @@ _FEW30 = tuple(1 + i % 5 for i in range(30))
 
 SKINNY = [
     # (segment sizes, spare rows, d, d_ff, tokens gathered from); capacity of at
-    # most 64 rows per segment. The 16-column kernel (few rows; W: ring
-    # workgroups of 64 columns over the segments that can have rows):
+    # most 64 rows per segment. The 16-column kernel in both GEMMs:
     ((1,), 0, 8, 8, None),                                # K below one pair, half a column tile
     ((16, 17, 33, 65) + (0,) * 8, 3, 256, 72, None),      # every row-tile count, two and three passes
     ((15, 0, 48, 1), 0, 1032, 40, 30),                    # K = whole pairs + 8 columns, gathered
     ((1, 0, 3), 0, 2184, 1096, None),                     # gate/up: two batches and a tail; down: six pairs, a tail
     ((2, 17), 2, 136, 1608, 9),                           # down: two batches of four pairs and a tail
-    (_FEW30, 6, 128, 640, None),                          # gate/up W = 300, ring down
-    (_FEW30, 5, 640, 64, 40),                             # gate/up W = 30, down W = 300 (K one pair)
-    # rows * W on either side of the line in gate/up (3072 and 3264)
+    # 30 segments of 1 to 5 rows: in gate/up, then in down (K one pair), the
+    # second round of the ring kernel's workgroups or (640 columns) not
+    (_FEW30, 6, 128, 832, None), (_FEW30, 6, 128, 640, None), (_FEW30, 5, 832, 64, 40), (_FEW30, 5, 640, 64, 40),
+    # a quarter of the CUs in gate/up: under it, under it with more empty segments, past it
     ((30, 20, 14) + (0,) * 13, 0, 192, 192, None), ((30, 20, 14) + (0,) * 14, 0, 192, 192, None),
-    # the other two kernels: more segments than lanes, some empty; ragged K; two
-    # and three passes; K of 4 and 6 chunks
+    ((30, 20, 14) + (0,) * 19, 0, 192, 192, None),
+    # the other two kernels (down of 24 and 328 columns: the 16-column one): more
+    # segments than lanes, some empty; ragged K; two and three passes; K of 4 and
+    # 6 chunks
     ((16, 17, 32, 33, 64, 65, 0), 3, 256, 72, None),
     (tuple((7 * i) % 5 for i in range(100)), 20, 64, 24, 40),
     (tuple(1 + i % 3 for i in range(60)), 40, 320, 328, None),

@@ -24,3 +24,38 @@ def test_gemm_without_a_cu_count(device, tmp_path):
         (name, grid), = launches  # one GEMM, no fixup
         assert "grouped_gemm_dma_kernel" in name
         assert grid[0] >= 8 and grid[0] % 8 == 0 and grid[1:] == (1, 1)
+
+
+RING, REG = "skinny_dma_kernel", "skinny_reg_kernel"
+SKINNY = [
+    # (GEMM, segments, rows, d, d_ff, kernel): both sides of every line of the
+    # rule, at sizes where the kernels were timed
+    ("up", 15, 4, 2048, 1408, REG), ("up", 15, 8, 2048, 1408, REG), ("up", 60, 8, 2048, 1408, RING),
+    ("up", 64, 6, 2048, 1408, RING), ("up", 8, 6, 4096, 1792, REG), ("up", 8, 12, 4096, 1792, RING),
+    ("up", 60, 48, 2048, 352, REG), ("up", 60, 128, 2048, 352, RING), ("up", 15, 240, 2048, 176, REG),
+    ("up", 15, 48, 2048, 1408, RING), ("up", 15, 96, 2048, 1408, REG), ("up", 15, 160, 2048, 1408, RING),
+    ("up", 8, 16, 4096, 3584, REG), ("up", 8, 96, 4096, 3584, RING),
+    ("up", 1, 16, 2048, 2816, REG), ("down", 1, 16, 2048, 2816, REG), ("down", 2, 32, 2048, 2816, REG),
+    ("down", 15, 4, 2048, 1408, REG), ("down", 60, 96, 2048, 1408, REG), ("down", 60, 128, 2048, 1408, RING),
+    ("down", 15, 96, 2048, 1408, REG), ("down", 15, 112, 2048, 1408, RING),
+    ("down", 4, 12, 4096, 14336, REG), ("down", 8, 2, 4096, 14336, REG), ("down", 8, 4, 4096, 14336, RING),
+    ("down", 8, 6, 4096, 3584, RING), ("down", 8, 16, 4096, 14336, REG),
+    ("down", 8, 48, 4096, 14336, RING), ("down", 8, 64, 4096, 3584, RING), ("down", 8, 96, 4096, 1792, RING),
+    ("down", 15, 240, 2048, 176, REG), ("down", 15, 241, 2048, 176, "skinny_gemm_kernel"),
+]
+
+
+def test_skinny_gemm_choice(tmp_path):
+    """Decode-sized GEMMs: the 16-column kernel only where it is the faster one."""
+    calls = [ffn_part(p, n, rows, d, f) for p, n, rows, d, f, _ in SKINNY]
+    for case, (status, launches) in zip(SKINNY, record(calls, tmp_path)):
+        assert status == OK
+        (name, _), = launches
+        assert case[-1] in name, (case, name)
+
+
+def test_skinny_gemm_choice_follows_the_cu_count(tmp_path):
+    """On half of the chip (128 CUs) the ring kernel is full twice as early."""
+    calls = [ffn_part("up", 15, 4, 2048, f, cus=cus, device=1 + i)
+             for i, (f, cus) in enumerate(((1408, 256), (1408, 128), (352, 128)))]
+    assert [[k for k in (RING, REG) if k in launches[0][0]] for _, launches in record(calls, tmp_path)] == [[REG], [RING], [REG]]
