@@ -535,9 +535,9 @@ __global__ __launch_bounds__(kSkThreads, 2) void skinny_reg_kernel(SkinnyParams 
 //    33.1. K of fewer than 512 whole columns gives the waves too little to load (60
 //    segments, d = d_ff = 256, 48 rows 1.1 of the ring kernel's time); ragged K
 //    competes with the slower register-staged kernel;
-//  - the ring kernel's second round of workgroups, as long as it is under half
-//    full: 15 segments, 64 rows 31.7 / 29.9, 96 rows 39.0 / 32.5; d = 4096,
-//    d_ff = 3584, 16 rows 74.7 / 68.1, but 96 rows 90.4 / 98.2;
+//  - the ring kernel's second round of workgroups, up to half full: 15
+//    segments, 64 rows 31.7 / 29.9, 96 rows 39.0 / 32.5; d = 4096, d_ff = 3584,
+//    16 rows 74.7 / 68.1, 48 rows (the line) 87-93 / 88, but 96 rows 90.4 / 98.2;
 //  - so few columns that the ring kernel never fills a quarter of the CUs: d_ff =
 //    176, 16 rows 15.2 / 8.4, 240 rows 15.4 / 13.5.
 //  down:
@@ -572,7 +572,7 @@ bool takes_reg(const SkinnyParams& p) {
         const double few = rows < 2 * n ? 0.45 : (double)most <= 0.5 * cus ? 0.45 : 0.0;
         const bool long_k = p.K >= 512 || p.K % kS2KC;
         return (long_k && rows <= (n > 6 ? 8 * n : 48) && busy <= few * cus) ||
-               (busy > cus && busy <= 1.45 * cus && (double)most <= 2.0 * cus);
+               (busy > cus && busy <= 1.5 * cus && (double)most <= 2.0 * cus);
     }
     if (p.K % kS2KC && p.K <= 512) return true;
     const bool in_flight = p.K <= 6 * 4 * 64;  // all of K (launch_skinny)
