@@ -1372,14 +1372,37 @@ size_t ffn_workspace_bytes() {
     return P > 0 ? (size_t)2 * P * kSkSlotBytes : 0;
 }
 
-// Whether a bf16 GEMM over K columns (above the skinny kernels' batch size)
-// runs on the persistent kernel with direct-to-LDS copies: K of whole 64-column
-// K-steps, or of at least three K-steps with a ragged last one (a shorter ragged
-// K would put the ragged step into the previous tile's copies). It is faster
-// than the register-staged tiles at any group size: 1.5-2.4x from 80 rows per
-// group up (d = 2048, d_ff = 1408); d_ff = 176 (T = 4096, 15 groups, top-4):
-// layer 200 -> 131 us.
-static bool gemm_dma_fits(int K) { return K % kDmaBK == 0 || K > 2 * kDmaBK; }
+// Whether a bf16 GEMM (above the skinny kernels' batch size) runs on the
+// persistent kernel with direct-to-LDS copies. K of whole 64-column K-steps
+// always does: it is faster than the register-staged tiles at any group size,
+// 1.5-2.4x from 80 rows per group up (d = 2048, d_ff = 1408). Ragged K does from
+// three K-steps on (a shorter one would put its ragged step into the previous
+// tile's copies): d_ff = 176 (T = 4096, 15 groups, top-4) layer 200 -> 131 us.
+// But with few K-steps the time is in the copies' latency and the epilogue, and
+// where the register-staged 128-row tiles are one round of workgroups at most,
+// they spread both over twice as many CUs. us, persistent / register-staged:
+//  - down, 15 groups of a Zipf law, d = 2048, d_ff = 176: T 300 17.5 / 15.3, 500
+//    17.9 / 15.9, 700 (two rounds) 18.9 / 27.6; 4 groups, 1000 rows, N = 2048: K
+//    136 18.0 / 13.8, 352 21.0 / 17.7, 616 26.6 / 23.1, 744 28.6 / 25.8, 1000
+//    33.5 / 32.4; the fuller the round, the shorter K has to be: 15 groups, T 500,
+//    K 488 24.7 / 25.2. Groups of fewer than 128 rows take half tiles on the
+//    persistent kernel: 15 even groups of 70 rows, N = 2048 K 176 13.4 / 15.3, K
+//    352 15.5 / 19.8 (the same rows by the Zipf law: 17.0 / 15.4, 20.1 / 19.4);
+//  - gate/up, 4 groups, 1000 rows, N = 1024: K 136 17.5 / 15.3, 392 22.7 / 20.1,
+//    520 24.6 / 22.7, 776 29.6 / 28.6; 15 groups, 1950 rows (a nearly full round)
+//    K 264 20.1 / 20.6; 15 even groups of 70 rows K 200 13.8 / 18.1.
+template <bool GATED>
+static bool gemm_dma_fits(const GemmParams& g) {
+    if (g.K % kDmaBK == 0) return true;
+    if (g.K <= 2 * kDmaBK) return false;
+    const int64_t cus = persistent_workgroups(), rows = g.rows_cap, n = g.n_seg;
+    const int64_t tiles = (ceil_div64(rows, 128) + n) * ceil_div(g.N, GATED ? 128 : 256);  // register-staged, at most
+    if (tiles > cus) return true;
+    const bool tall = rows >= 96 * n;  // groups past a half tile on average, nearly
+    const bool staged = GATED ? tall && g.K < 448 && g.K * tiles <= 300 * cus
+                              : (tall || g.K <= 256) && g.K <= 640 && g.K * tiles <= 448 * cus;
+    return !staged;
+}
 
 bool ffn_can_fold(const FfnArgs& a) {
     return a.dtype == BMOE_BF16 && a.rows_cap > 0 && !ffn_skinny_fits(a) && a.d_ff % kDmaBK == 0 && a.d % kDmaBK == 0 &&
@@ -1397,8 +1420,8 @@ hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {
         g1.a_rows = a.a_rows;
         g1.a_count = a.a_count;
         g1.sk_min_idle = a.split_min_idle;
-        hipError_t e = gemm_dma_fits(g1.K) ? launch_gemm_dma<true>(g1, a.ws, a.ws_bytes, s)
-                                           : launch_gemm<true, 128, 128, 64, true>(g1, s);
+        hipError_t e = gemm_dma_fits<true>(g1) ? launch_gemm_dma<true>(g1, a.ws, a.ws_bytes, s)
+                                               : launch_gemm<true, 128, 128, 64, true>(g1, s);
         if (e != hipSuccess) return e;
     }
     if (down) {
@@ -1406,8 +1429,8 @@ hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {
                       a.offsets, a.n_seg, a.rows_cap, a.d, a.d_ff};
         g2.sk_min_idle = a.split_min_idle;
         g2.fold = a.fold;
-        return gemm_dma_fits(g2.K) ? launch_gemm_dma<false>(g2, a.ws, a.ws_bytes, s)
-                                   : launch_gemm<false, 128, 256, 64, true>(g2, s);
+        return gemm_dma_fits<false>(g2) ? launch_gemm_dma<false>(g2, a.ws, a.ws_bytes, s)
+                                        : launch_gemm<false, 128, 256, 64, true>(g2, s);
     }
     return hipSuccess;
 }

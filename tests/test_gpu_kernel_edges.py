@@ -97,20 +97,31 @@ def ffn_workspace():
 TILE_FFN = [
     # (segment sizes, rows_cap, d, d_ff, tokens gathered from), above the skinny
     # kernels' size: tails on either side of half a 256-row tile, segments of a
-    # half tile only, ragged last K-steps of every width (8 to 56 columns,
-    # three K-steps and more) in either GEMM, column remainders
+    # half tile only, column remainders
     ((128, 129, 256, 257, 1, 0, 384, 385), 1600, 320, 192, None),
+    # ragged K of few rows (one round of workgroups): the register-staged tiles
     ((128, 127, 512, 1), 800, 136, 176, None),
     ((300, 64), 400, 184, 200, 150),
     ((130, 700), 900, 168, 136, None),
     ((513, 40, 0, 200), 800, 152, 144, 300),
     ((250, 255, 3), 600, 312, 248, None),
+    # the same with empty segments, so that the rows are few per segment: the
+    # persistent kernel with ragged last K-steps of 8 to 56 columns, three
+    # K-steps and more
+    ((128, 127, 512, 1) + (0,) * 5, 800, 136, 304, None),
+    ((300, 64) + (0,) * 3, 400, 184, 328, 150),
+    ((130, 700) + (0,) * 8, 900, 168, 264, None),
+    ((513, 40, 0, 200) + (0,) * 6, 800, 152, 280, 300),
+    ((250, 255, 3) + (0,) * 6, 600, 312, 376, None),
+    # and for so many segments that the register-staged tiles might not be one round: three K-steps in down
+    ((200, 129) + (3,) * 19 + (0,) * 110, 8400, 512, 136, None),
     # more half tiles than workgroups: 60 segments x 5 column tiles of gate/up
     (tuple(1 + (37 * i) % 128 for i in range(60)), 5000, 128, 584, None),
     # whole tiles and half tiles in the same round, half tiles in the next
     (tuple([256] * 20 + [100] * 30), 8400, 192, 1160, None),
     # ragged K too short for the copies: the register-staged tiles
     ((200, 130), 400, 72, 104, None),
+    ((300, 1, 0, 129), 450, 120, 88, 200),
 ]
 
 
@@ -124,8 +135,10 @@ def test_ffn_tile_heights_and_ragged_k(sizes, cap, d, f, tokens, stream_k):
         check_ffn(sizes, cap, d, f, "bf16", 1, tokens, ffn_workspace() if stream_k else None, 0 if stream_k else None)
 
 
-@pytest.mark.parametrize("part,K,rows", [("up", 200, 150), ("up", 152, 700), ("down", 176, 150), ("down", 312, 700),
-                                         ("up", 72, 150), ("down", 120, 150), ("up", 328, 10), ("down", 72, 10)])
+# the persistent kernel; the register-staged tiles; the 16-column kernel
+@pytest.mark.parametrize("part,K,rows", [("up", 456, 150), ("up", 520, 700), ("down", 648, 150), ("down", 696, 700),
+                                         ("up", 200, 150), ("down", 176, 150), ("up", 72, 150), ("down", 120, 150),
+                                         ("up", 328, 10), ("down", 72, 10)])
 def test_ffn_infinite_weights_ragged_k(part, K, rows):
     """An infinite weight in the last 64-column step of a ragged K: the step's
     padding must not turn it into NaN (0 * inf). Exact inputs (one-hot rows and

@@ -59,3 +59,30 @@ def test_skinny_gemm_choice_follows_the_cu_count(tmp_path):
     calls = [ffn_part("up", 15, 4, 2048, f, cus=cus, device=1 + i)
              for i, (f, cus) in enumerate(((1408, 256), (1408, 128), (352, 128)))]
     assert [[k for k in (RING, REG) if k in launches[0][0]] for _, launches in record(calls, tmp_path)] == [[REG], [RING], [REG]]
+
+
+TILES = [
+    # (GEMM, segments, rows, d, d_ff, kernel): ragged K, where the register-staged
+    # 128-row tiles are one round of workgroups at most, and past it
+    ("down", 15, 1200, 2048, 176, "grouped_gemm_kernel<false, 128"), ("down", 15, 2000, 2048, 176, "grouped_gemm_kernel<false, 128"),
+    ("down", 15, 2800, 2048, 176, "dma_kernel<false, true"), ("down", 15, 1200, 2048, 352, "dma_kernel<false, true"),
+    ("down", 15, 1600, 2048, 352, "grouped_gemm_kernel<false, 128"), ("down", 15, 2000, 2048, 488, "dma_kernel<false, true"),
+    ("down", 4, 1000, 2048, 616, "grouped_gemm_kernel<false, 128"), ("down", 4, 1000, 2048, 744, "dma_kernel<false, true"),
+    ("down", 4, 1000, 2048, 192, "dma_kernel<false, true"),
+    ("up", 4, 1000, 136, 1024, "grouped_gemm_kernel<true, 128"), ("up", 4, 1000, 392, 1024, "grouped_gemm_kernel<true, 128"),
+    ("up", 4, 1000, 520, 1024, "dma_kernel<true, true"), ("up", 15, 1050, 200, 1024, "dma_kernel<true, true"),
+    ("up", 15, 1950, 392, 1024, "dma_kernel<true, true"),
+    # the half tiles' line in rows per segment, K whole
+    ("up", 15, 15 * 768 - 1, 2048, 1408, "dma_kernel<true, true"), ("up", 15, 15 * 768, 2048, 1408, "dma_kernel<true, false"),
+    # K too short for the copies
+    ("up", 4, 1000, 72, 1024, "grouped_gemm_kernel<true, 128"), ("down", 4, 1000, 1024, 120, "grouped_gemm_kernel<false, 128"),
+]
+
+
+def test_large_gemm_choice(tmp_path):
+    """Larger GEMMs: register-staged tiles where they are faster (or the only ones), else the persistent kernel."""
+    calls = [ffn_part(p, n, rows, d, f) for p, n, rows, d, f, _ in TILES]
+    for case, (status, launches) in zip(TILES, record(calls, tmp_path)):
+        assert status == OK
+        (name, _), = launches
+        assert case[-1] in name, (case, name)
