@@ -5,14 +5,15 @@
 //
 // bf16 path, above the skinny kernels' batch size: the persistent kernel with
 // direct-to-LDS copies (grouped_gemm_dma_kernel, below). K too short and ragged
-// for it (at most 128 columns, not whole 64-column K-steps) takes
-// grouped_gemm_kernel: 256 threads (4 waves, 2x2), 32x32x16 bf16 MFMA with fp32
-// accumulation, A and B tiles double-buffered in LDS with padded rows
-// (conflict-free 128-bit fragment reads), global loads of the next K-step in
-// flight while the current one runs on the matrix cores.
+// for it (at most 128 columns, not whole 64-column K-steps), and a short ragged K
+// of few rows (gemm_dma_fits), take grouped_gemm_kernel: 256 threads (4 waves,
+// 2x2), 32x32x16 bf16 MFMA with fp32 accumulation, A and B tiles double-buffered
+// in LDS with padded rows (conflict-free 128-bit fragment reads), global loads of
+// the next K-step in flight while the current one runs on the matrix cores.
 //   gate/up: BM=128, BN=128 columns of BOTH W_gate and W_up (each wave 64x64 of
 //            each), epilogue silu(g)*u -> bf16 h;
-//   down:    BM=128, BN=256 (each wave 64x128), epilogue -> bf16 y.
+//   down:    BM=128, BN=256 (each wave 64x128), epilogue -> bf16 y;
+//   or BM=256 (128x64 of each matrix, 128x128 per wave), see launch_gemm_staged.
 // Its grid covers the worst case (ceil(rows_cap/BM) + n_seg M-tiles times the
 // N-tiles); every workgroup rebuilds the per-segment M-tile prefix from the
 // device offsets (no host sync), maps its (XCD-swizzled) id to (segment,
@@ -279,6 +280,8 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grouped_gemm_kernel(GemmParam
             *(uint4*)(p.C + (size_t)gm * N + gn) = *(const uint4*)(st + r * C::SROW + cc * 8);
     }
 }
+
+constexpr bool kFdb256 = false;  // 256-row tiles leave no registers for a second fragment set
 
 template <bool GATED, int BM, int BN, int BK, bool FDB>
 hipError_t launch_gemm(const GemmParams& g, hipStream_t s) {
@@ -1409,6 +1412,27 @@ bool ffn_can_fold(const FfnArgs& a) {
            a.d % 128 == 0 && stream_k_workgroups() > 0;
 }
 
+// The register-staged tiles of K that the persistent kernel does not take. With
+// 1024 rows per segment and K of one or two K-steps, 256-row tiles read B half as
+// often and take 1.34 times as long in gate/up (1.77 times in down) as 128-row
+// ones, so they run where they are that many fewer rounds of workgroups. us, 128-
+// / 256-row: gate/up, 4 groups, d = 72, d_ff = 4096, 8000 rows 130 / 114, 20000
+// rows 257 / 241; d_ff = 1024, 5000 rows 27.7 / 25.3, 12000 rows 53.3 / 47.6; d =
+// d_ff = 120, 8000 rows 13.8 / 23.1; down, d = 1024, d_ff = 72, 5000 rows 13.7 /
+// 21.9, 8000 rows 24.5 / 22.5, 20000 rows 35.8 / 42.5. (Rounds by the capacity: a
+// round that the real rows just miss costs more, 8000 rows of d_ff = 1024 40 / 47.)
+template <bool GATED>
+static hipError_t launch_gemm_staged(const GemmParams& g, hipStream_t s) {
+    constexpr int BN = GATED ? 128 : 256;
+    if (g.K <= 2 * kDmaBK && (int64_t)g.rows_cap >= (int64_t)1024 * g.n_seg) {
+        const int64_t cus = persistent_workgroups(), nt = ceil_div(g.N, BN);
+        auto rounds = [&](int bm) { return ceil_div64((ceil_div64(g.rows_cap, bm) + g.n_seg / 2) * nt, cus); };
+        if (GATED ? 4 * rounds(256) <= 3 * rounds(128) : 7 * rounds(256) <= 4 * rounds(128))
+            return launch_gemm<GATED, 256, BN, 64, kFdb256>(g, s);
+    }
+    return launch_gemm<GATED, 128, BN, 64, true>(g, s);
+}
+
 hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {
     if (a.rows_cap == 0) return hipSuccess;
     const bool up = part != 2, down = part != 1;
@@ -1421,7 +1445,7 @@ hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {
         g1.a_count = a.a_count;
         g1.sk_min_idle = a.split_min_idle;
         hipError_t e = gemm_dma_fits<true>(g1) ? launch_gemm_dma<true>(g1, a.ws, a.ws_bytes, s)
-                                               : launch_gemm<true, 128, 128, 64, true>(g1, s);
+                                               : launch_gemm_staged<true>(g1, s);
         if (e != hipSuccess) return e;
     }
     if (down) {
@@ -1430,7 +1454,7 @@ hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {
         g2.sk_min_idle = a.split_min_idle;
         g2.fold = a.fold;
         return gemm_dma_fits<false>(g2) ? launch_gemm_dma<false>(g2, a.ws, a.ws_bytes, s)
-                                        : launch_gemm<false, 128, 256, 64, true>(g2, s);
+                                        : launch_gemm_staged<false>(g2, s);
     }
     return hipSuccess;
 }

@@ -119,8 +119,11 @@ TILE_FFN = [
     (tuple(1 + (37 * i) % 128 for i in range(60)), 5000, 128, 584, None),
     # whole tiles and half tiles in the same round, half tiles in the next
     (tuple([256] * 20 + [100] * 30), 8400, 192, 1160, None),
-    # ragged K too short for the copies: the register-staged tiles
+    # ragged K too short for the copies: the register-staged tiles, of 128 rows,
+    # then of 256 rows in one of the GEMMs
     ((200, 130), 400, 72, 104, None),
+    ((2600, 0, 257, 1), 5000, 72, 1024, 3000),
+    ((4000, 255), 7000, 1032, 120, None),
     ((300, 1, 0, 129), 450, 120, 88, 200),
 ]
 

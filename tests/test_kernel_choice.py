@@ -74,7 +74,12 @@ TILES = [
     ("up", 15, 1950, 392, 1024, "dma_kernel<true, true"),
     # the half tiles' line in rows per segment, K whole
     ("up", 15, 15 * 768 - 1, 2048, 1408, "dma_kernel<true, true"), ("up", 15, 15 * 768, 2048, 1408, "dma_kernel<true, false"),
-    # K too short for the copies
+    # K too short for the copies; 256-row tiles where they are enough fewer rounds
+    ("up", 4, 8000, 72, 4096, "grouped_gemm_kernel<true, 256"), ("up", 4, 5000, 72, 1024, "grouped_gemm_kernel<true, 256"),
+    ("up", 4, 8000, 120, 120, "grouped_gemm_kernel<true, 128"),
+    ("up", 8, 8184, 72, 4096, "grouped_gemm_kernel<true, 128"), ("up", 4, 8000, 136, 4096, "dma_kernel<true, true"),
+    ("down", 4, 5000, 1024, 72, "grouped_gemm_kernel<false, 128"), ("down", 4, 8000, 1024, 72, "grouped_gemm_kernel<false, 256"),
+    ("down", 4, 20000, 1024, 72, "grouped_gemm_kernel<false, 128"),
     ("up", 4, 1000, 72, 1024, "grouped_gemm_kernel<true, 128"), ("down", 4, 1000, 1024, 120, "grouped_gemm_kernel<false, 128"),
 ]
 
