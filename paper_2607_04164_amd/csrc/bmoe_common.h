@@ -150,7 +150,8 @@ struct DistillArgs {
     void* ws;               // distill_ws_bytes(G, T)
     int E, G, T, d, dtype;
 };
-int distill_blocks(int G, int T);
+// workgroups per group that the workspace and the size limit are for
+int distill_ws_blocks(int G, int T);
 size_t distill_ws_bytes(int G, int T);
 hipError_t launch_distill_mse(const DistillArgs& a, hipStream_t s);
 

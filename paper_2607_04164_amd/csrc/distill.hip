@@ -148,29 +148,31 @@ __global__ __launch_bounds__(kDThreads) void distill_partial_kernel(const int32_
     const int r = blockIdx.y, nb = gridDim.x, b = blockIdx.x;
     const int n = group_members(e2g, w, E, r, s_mem, s_w, s_cnt);
     group_alphas(s_w, n, s_alpha);
-    const int nch = d / EPC;
+    const uint32_t nch = d / EPC;
     const int t0 = (int)((int64_t)T * b / nb), t1 = (int)((int64_t)T * (b + 1) / nb);
-    const int nc = (t1 - t0) * nch;  // chunks of this workgroup (the host bounds T d / nb)
+    // chunks of this workgroup: under 5/4 of 2^31 (the host bounds those of distill_ws_blocks workgroups per group)
+    const uint32_t nc = (uint32_t)(t1 - t0) * nch;
     double acc = 0.0;
     if (n > 0) {
         // two chunks per thread and step, every load of both issued before any
         // is used (four members' loads at once measured the same); squares
         // added in chunk order
         constexpr int U = 2;
-        for (int c0 = threadIdx.x; c0 < nc; c0 += U * kDThreads) {
+        for (uint32_t c0 = threadIdx.x; c0 < nc; c0 += U * kDThreads) {
             float tv[U][EPC], u[U][EPC];
 #pragma unroll
             for (int q = 0; q < U; ++q)
 #pragma unroll
                 for (int i = 0; i < EPC; ++i) tv[q][i] = 0.f;
             bool ok[U];
-            int t[U], j[U];
+            int t[U];
+            uint32_t j[U];
 #pragma unroll
             for (int q = 0; q < U; ++q) {
-                const int c = c0 + q * kDThreads;
+                const uint32_t c = c0 + q * kDThreads;
                 ok[q] = c < nc;
-                const int cc = ok[q] ? c : 0;
-                t[q] = t0 + cc / nch;
+                const uint32_t cc = ok[q] ? c : 0;
+                t[q] = t0 + (int)(cc / nch);
                 j[q] = cc % nch;
             }
             for (int m = 0; m < n; ++m) {
@@ -264,17 +266,19 @@ __global__ __launch_bounds__(kDFinal) void distill_final_kernel(const int32_t* _
 
 }  // namespace
 
-int distill_blocks(int G, int T) {
+static int distill_blocks(int G, int T) {
     // four workgroups per CU, all resident at once (measured: 512 or 2048 in
     // all were slower), at most one per token
     int nb = 1024 / G;
     return nb < T ? nb : T;
 }
 
-size_t distill_ws_bytes(int G, int T) {
-    const int nb = (1024 + G - 1) / G;  // (a little more than the partials of distill_blocks)
-    return (size_t)(nb < T ? nb : T) * G * sizeof(double);
+int distill_ws_blocks(int G, int T) {
+    const int nb = (1024 + G - 1) / G;  // (up to 5/4 of distill_blocks)
+    return nb < T ? nb : T;
 }
+
+size_t distill_ws_bytes(int G, int T) { return (size_t)distill_ws_blocks(G, T) * G * sizeof(double); }
 
 hipError_t launch_united_init(const UnitedInitArgs& a, hipStream_t s) {
     const int64_t elems_gu = (int64_t)a.d_ff * a.d;  // gate/up and down hold the same count

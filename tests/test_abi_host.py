@@ -174,6 +174,10 @@ def test_entry_points_reject_before_launch(lib):
     assert dm(1, 8, 4, 100, 256, FAKE, FAKE, FAKE, FAKE, FAKE, z, z, W, z) == WS
     assert dm(1, 8, 4, 100, 256, FAKE, FAKE, FAKE, FAKE, FAKE, z, FAKE, 64, z) == WS
     assert dm(1, 8, 4, 0, 256, z, z, z, z, z, z, z, 0, z) == OK
+    # the largest accepted size (of six workgroups per group), and the next one
+    most = 2 ** 31 - 6
+    assert dm(1, 200, 200, most, 40, z, z, z, z, z, z, z, 0, z) == NULL
+    assert dm(1, 200, 200, most, 48, z, z, z, z, z, z, z, 0, z) == SHAPE
     # combine
     assert lib.brownout_moe_combine(bd, FAKE, FAKE, FAKE, z, z, z) == NULL
     assert lib.brownout_moe_combine(bd, FAKE, FAKE, FAKE, MISALIGNED, FAKE, z) == ALIGN
