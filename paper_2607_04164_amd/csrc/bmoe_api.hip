@@ -265,7 +265,7 @@ bmoe_status brownout_moe_distill_mse(int32_t dtype, int32_t E, int32_t G, int32_
     if (T == 0) return BMOE_OK;
     const int nb = bmoe::distill_ws_blocks(G, T);
     // the partial kernel counts a workgroup's chunks in 32 bits
-    if ((int64_t)((T + nb - 1) / nb + 1) * (d / (dtype == BMOE_BF16 ? 8 : 4)) >= ((int64_t)1 << 31))
+    if ((((int64_t)T + nb - 1) / nb + 1) * (d / (dtype == BMOE_BF16 ? 8 : 4)) >= ((int64_t)1 << 31))
         return BMOE_ERR_SHAPE;
     if (!e2g || !w_freq || !y_expert || !y_united || !mse) return BMOE_ERR_NULL;
     if (!aligned16(y_expert) || !aligned16(y_united) || ((uintptr_t)mse & 7u) || ((uintptr_t)mse_total & 7u))

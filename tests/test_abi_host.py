@@ -178,6 +178,7 @@ def test_entry_points_reject_before_launch(lib):
     most = 2 ** 31 - 6
     assert dm(1, 200, 200, most, 40, z, z, z, z, z, z, z, 0, z) == NULL
     assert dm(1, 200, 200, most, 48, z, z, z, z, z, z, z, 0, z) == SHAPE
+    assert dm(1, 200, 200, 2 ** 31 - 1, 48, z, z, z, z, z, z, z, 0, z) == SHAPE  # (T + 5 is past 32 bits)
     # combine
     assert lib.brownout_moe_combine(bd, FAKE, FAKE, FAKE, z, z, z) == NULL
     assert lib.brownout_moe_combine(bd, FAKE, FAKE, FAKE, MISALIGNED, FAKE, z) == ALIGN
