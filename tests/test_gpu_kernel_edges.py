@@ -115,6 +115,9 @@ TILE_FFN = [
     ((250, 255, 3) + (0,) * 6, 600, 312, 376, None),
     # and for so many segments that the register-staged tiles might not be one round: three K-steps in down
     ((200, 129) + (3,) * 19 + (0,) * 110, 8400, 512, 136, None),
+    # whole tiles only (768 rows per segment of capacity), a column remainder of
+    # 48 in gate/up (a tensor-parallel share)
+    ((1000, 0, 513, 1), 4096, 320, 176, None),
     # more half tiles than workgroups: 60 segments x 5 column tiles of gate/up
     (tuple(1 + (37 * i) % 128 for i in range(60)), 5000, 128, 584, None),
     # whole tiles and half tiles in the same round, half tiles in the next
@@ -128,14 +131,42 @@ TILE_FFN = [
 ]
 
 
-@pytest.mark.parametrize("stream_k", [False, True], ids=["whole", "stream_k"])
-@pytest.mark.parametrize("sizes,cap,d,f,tokens", TILE_FFN, ids=[f"seg{len(c[0])}-d{c[2]}-f{c[3]}" for c in TILE_FFN])
-def test_ffn_tile_heights_and_ragged_k(sizes, cap, d, f, tokens, stream_k):
+# with the split threshold at zero and the workspace, where a K is whole K-steps
+# (a ragged K is never split; ffn_gather takes no threshold)
+TILE_RUNS = [(c, False) for c in TILE_FFN] + [(c, True) for c in TILE_FFN if c[4] is None and min(c[2] % 64, c[3] % 64) == 0]
+
+
+@pytest.mark.parametrize("case,stream_k", TILE_RUNS,
+                         ids=[f"seg{len(c[0])}-d{c[2]}-f{c[3]}{'-stream_k' if k else ''}" for c, k in TILE_RUNS])
+def test_ffn_tile_heights_and_ragged_k(case, stream_k):
+    sizes, cap, d, f, tokens = case
     assert cap > 64 * len(sizes) and sum(sizes) <= cap
-    if stream_k and tokens is not None:
-        check_ffn(sizes, cap, d, f, "bf16", 1, tokens, ffn_workspace())
+    if stream_k:
+        check_ffn(sizes, cap, d, f, "bf16", 1, None, ffn_workspace(), 0)
     else:
-        check_ffn(sizes, cap, d, f, "bf16", 1, tokens, ffn_workspace() if stream_k else None, 0 if stream_k else None)
+        check_ffn(sizes, cap, d, f, "bf16", 1, tokens)
+
+
+def test_ffn_tails_of_wide_weights():
+    """Half tiles read their segment's weights again: past 256 MB of that, the
+    tails of segments with whole tiles stay whole while segments of at most 128
+    rows keep half tiles. Against fp32 products of the same bf16 values."""
+    sizes, d, f = (300, 350, 60, 270, 380, 128), 4096, 4160
+    assert sum(s > 256 and 0 < s % 256 <= 128 for s in sizes) * 2 * d * f * 2 > 256 << 20
+    n, cap = len(sizes), sum(sizes) + 40
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(cap, d, generator=gen, device="cuda").bfloat16()
+    wg, wu = ((torch.randn(n, f, d, generator=gen, device="cuda") / d ** 0.5).bfloat16() for _ in range(2))
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(sizes)]), dtype=torch.int32, device="cuda")
+    h = torch.full((cap, f), -5.0, dtype=torch.bfloat16, device="cuda")
+    B.ffn_gate_up(offsets, x, wg, wu, h=h)
+    beg = 0
+    for s, rows in enumerate(sizes):
+        a = x[beg:beg + rows].float()
+        want = torch.nn.functional.silu(a @ wg[s].float().t()) * (a @ wu[s].float().t())
+        assert_close_rows(host_f32(h[beg:beg + rows]), want.cpu().numpy(), "bf16", f"h of segment {s}")
+        beg += rows
+    assert bool((h[beg:] == -5.0).all())
 
 
 # the persistent kernel; the register-staged tiles; the 16-column kernel
@@ -213,9 +244,13 @@ ROUTE = [
     # (experts, d, top_k, tokens): rings of the waves' own with fewer chunks than
     # waves, more chunks than slots, ragged token tiles of 16 (up to 4096 tokens)
     # and 32, one and four blocks of experts, picks past the register list; then
-    # both sides of their rules (d not whole chunks, more experts, more tokens)
+    # both sides of their rules (d not whole chunks, more experts, more tokens:
+    # x straight into registers for d of 512, 1024 and 2048, the shared ring with
+    # 16, 32 and 64 tokens per workgroup)
     (9, 64, 2, 40), (64, 64, 5, 17), (3, 320, 2, 33), (16, 192, 3, 4130), (40, 576, 9, 4110), (17, 2112, 4, 4096),
     (60, 2048, 4, 1), (12, 72, 3, 300), (65, 256, 4, 300), (33, 512, 3, 8193), (16, 640, 16, 50),
+    (33, 1024, 5, 8200), (60, 512, 9, 8200), (30, 72, 3, 200), (16, 640, 3, 8200), (40, 320, 2, 8300), (12, 128, 2, 16400),
+    (40, 192, 2, 16390),
 ]
 
 

@@ -33,8 +33,9 @@ SMALL = {
     "heavy-s": W.CONFIGS["heavy"].with_(name="heavy-s", T=700, d=512, d_ff=192, d_ff_shared_each=192),
     "decode": W.CONFIGS["decode"],
     "tail": W.LayerConfig("tail", T=33, d=264, E=12, top_k=3, G=5, d_ff=520, dtype="bf16", zipf_s=1.2),
-    # d_ff not a whole 64-column K-step: the register-staged 128-row tiles
-    # (whole 64-column K-steps take the persistent 256-row kernel at any size)
+    # d and d_ff not whole 64-column K-steps: gate/up on the persistent kernel
+    # with a ragged last K-step, down (fewer K-steps, one round of workgroups) on
+    # the register-staged 128-row tiles
     "ragged-s": W.CONFIGS["mixtral"].with_(name="ragged-s", T=300, d=520, d_ff=600),
 }
 CASES = [(n, 0) for n in SMALL] + [("tiny", 1), ("tiny", 2), ("fine-s", 1)]
@@ -93,13 +94,13 @@ def test_route_exact(name, seed):
     assert_gates(got["slot_gate"].cpu().numpy(), ref["slot_gate"], "slot_gate")
 
 
-@pytest.mark.parametrize("E,d,k", [(16, 256, 4), (8, 256, 4), (8, 4096, 4), (16, 256, 10)],
-                         ids=["ring-E16", "ring-E8", "direct-E8-d4096", "ring-E16-k10"])
+@pytest.mark.parametrize("E,d,k", [(16, 256, 4), (8, 256, 4), (8, 4096, 4), (16, 256, 10), (16, 264, 4)],
+                         ids=["rings-E16", "rings-E8", "direct-E8-d4096", "rings-E16-k10", "shared-ring-E16"])
 def test_route_near_ties_decided_in_f64(E, d, k):
     """Two experts whose logits differ by far less than the fp32 rounding error
-    (and exact ties) are still ordered as float64 orders them (on the LDS-ring
-    logits path, on the direct path of routers with at most 8 experts, and with
-    more picks than the register pick list holds)."""
+    (and exact ties) are still ordered as float64 orders them (with rings of
+    the waves' own, on the direct path of routers with at most 8 experts, with
+    more picks than the register pick list holds, and with the shared ring)."""
     cfg = W.LayerConfig("ties", T=96, d=d, E=E, top_k=k, G=4, d_ff=64, dtype="bf16", zipf_s=1.0)
     L = W.make_layer(cfg, 5)
     # expert 7's router row equals expert 3's except one bf16 ulp in column 17;
@@ -131,8 +132,8 @@ def test_route_near_ties_decided_in_f64(E, d, k):
                                      (17, 512, 3, 4100), (33, 1024, 5, 4111), (64, 2048, 6, 8200),
                                      (60, 2048, 9, 4096)],
                          ids=["direct-d1024", "direct-d2048", "direct-d3072", "direct-E5", "direct-E3-k1",
-                              "direct-k8", "ring-k9", "ring-E16-d1024", "xdirect-E17-d512", "xdirect-E33-d1024",
-                              "xdirect-2perCU", "xdirect-k9"])
+                              "direct-k8", "rings-k9", "rings-E16-d1024", "rings-E17-d512", "rings-E33-d1024",
+                              "xdirect-2perCU", "rings-E60-k9"])
 def test_route_shapes(E, d, k, T):
     """Every bf16 logits path and both pick lists (registers for k <= 8, LDS
     beyond) on ragged token counts: integers exact, gates to tolerance."""
@@ -333,13 +334,13 @@ _SIZES60 = tuple(0 if i % 7 == 0 else 3000 // (i + 1) for i in range(60))
 LARGE_TILE_FFN = [
     # (segment sizes, rows_cap, d, d_ff): above the skinny kernels' size, d and
     # d_ff multiples of 64 select the persistent direct-to-LDS kernel at any
-    # group size; otherwise rows_cap >= 1024 * segments selects the register-
-    # staged 256-row tiles
+    # group size; a ragged K of few K-steps, where they are one round of
+    # workgroups, the register-staged 128-row tiles
     ((700, 333), 2048, 256, 384),
     (_SIZES60, sum(_SIZES60) + 300, 256, 192),
     ((1000, 0, 513, 1), 4096, 320, 448),   # N tails in both GEMMs, empty and 1-row segments
     ((0, 1290), 2048, 512, 192),
-    ((1000, 0, 513, 1), 4096, 288, 352),   # not multiples of 64: register-staged 256-row kernels
+    ((1000, 0, 513, 1), 4096, 288, 352),   # not multiples of 64: register-staged tiles
     ((257,), 1024, 264, 200),
     # one and two K-steps per tile (K = 64, 128): the K loops without a
     # copying step, and stream-K pieces of a single K-step
@@ -603,8 +604,14 @@ def partial_layer(L):
 GATHER = {
     "tiny": SMALL["tiny"],                     # fp32 kernels
     "mixtral-s": SMALL["mixtral-s"],           # persistent 256-row tiles, 150 rows per group
-    "ragged-s": SMALL["ragged-s"],             # 128-row register-staged tiles
-    "decode": SMALL["decode"],                 # skinny weight-streaming kernels
+    "ragged-s": SMALL["ragged-s"],             # persistent tiles, a ragged last K-step in gate/up
+    # 128-row register-staged tiles: three K-steps, and too few for the copies
+    "ragged-136": SMALL["ragged-s"].with_(name="ragged-136", d=136),
+    "ragged-72": SMALL["ragged-s"].with_(name="ragged-72", d=72),
+    "tall-72": SMALL["ragged-s"].with_(name="tall-72", T=2600, d=72, d_ff=1024),  # and of 256 rows
+    "decode": SMALL["decode"],                 # skinny weight-streaming kernels: copies into LDS,
+    "decode-ragged": SMALL["decode"].with_(name="decode-ragged", d=520),  # through registers,
+    "decode-2": SMALL["decode"].with_(name="decode-2", T=2),              # 16 columns with K split
     "dma": W.LayerConfig("dma", T=2100, d=256, E=8, top_k=2, G=4, d_ff=384, dtype="bf16", zipf_s=0.5),
 }
 
