@@ -205,7 +205,7 @@ struct FfnArgs {
     const void* w_down;
     void* h;
     void* y;
-    void* ws;  // optional stream-K workspace (nullptr: one tile per workgroup)
+    void* ws;  // optional stream-K workspace (nullptr: every tile whole)
     size_t ws_bytes;
     int n_seg, rows_cap, d, d_ff, dtype;
     // gathered A operand of the gate/up GEMM: row r is a[a_rows[r]] (a has

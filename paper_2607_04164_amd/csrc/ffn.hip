@@ -44,8 +44,12 @@ struct GemmParams {
     FoldArgs fold;  // combine folded into the down projection's epilogue (out == nullptr: not folded)
 };
 
-template <bool GATED, int BM, int BN, int BK>
+// Register-staged tiles: BM 128 or 256 rows, 128 output columns of each of
+// W_gate and W_up or 256 of W_down, K-steps of 64.
+template <bool GATED, int BM_>
 struct GemmCfg {
+    static constexpr int BM = BM_, BN = GATED ? 128 : 256, BK = 64;
+    static constexpr bool FDB = BM == 128;  // fragments double-buffered (256 rows leave no registers for it)
     static constexpr int WM = 2, WN = 2;
     static constexpr int WTM = BM / WM, WTN = BN / WN;
     static constexpr int MB = WTM / 32, NB = WTN / 32;
@@ -152,9 +156,10 @@ __device__ __forceinline__ void gemm_mfmas(f32x16 (&acc)[C::NMAT][C::MB][C::NB],
             for (int nb = 0; nb < C::NB; ++nb) acc[mat][mb][nb] = mfma32(af[mb], bf[mat][nb], acc[mat][mb][nb]);
 }
 
-template <bool GATED, int BM, int BN, int BK, bool FDB>
+template <bool GATED, int BM>
 __global__ __launch_bounds__(kGemmThreads, 1) void grouped_gemm_kernel(GemmParams p) {
-    using C = GemmCfg<GATED, BM, BN, BK>;
+    using C = GemmCfg<GATED, BM>;
+    constexpr int BN = C::BN, BK = C::BK;
     __shared__ __align__(16) char smem[C::SMEM];
     __shared__ int s_scan[256];
     __shared__ int s_mt[BMOE_MAX_EXPERTS + 1];
@@ -226,7 +231,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grouped_gemm_kernel(GemmParam
         if (more) gemm_gload<C>(ra, rb, p.A, arow, Bm[0], Bm[1], tid, (kt + 1) * BK, n0, N, K);
         const uint16_t* a_base = sA + (size_t)(buf * BM + wm * C::WTM + l32) * C::LROW + hi8;
         const uint16_t* b_base = sB + (size_t)(buf * BN + wn * C::WTN + l32) * C::LROW + hi8;
-        if constexpr (FDB) {
+        if constexpr (C::FDB) {
             // fragments of sub-step kk+1 are read from LDS while sub-step kk runs on the MFMA pipe
             uint4 af[2][C::MB];
             uint4 bf[2][C::NMAT][C::NB];
@@ -281,58 +286,50 @@ __global__ __launch_bounds__(kGemmThreads, 1) void grouped_gemm_kernel(GemmParam
     }
 }
 
-constexpr bool kFdb256 = false;  // 256-row tiles leave no registers for a second fragment set
-
-template <bool GATED, int BM, int BN, int BK, bool FDB>
+template <bool GATED, int BM>
 hipError_t launch_gemm(const GemmParams& g, hipStream_t s) {
+    constexpr int BN = GemmCfg<GATED, BM>::BN;
     const int64_t mt_max = ceil_div64(g.rows_cap, BM) + g.n_seg;
     const int64_t nt = ceil_div64(g.N, BN);
     int64_t blocks = mt_max * nt;
     blocks = (blocks + 7) / 8 * 8;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((grouped_gemm_kernel<GATED, BM, BN, BK, FDB>), dim3((unsigned)blocks),
-                       dim3(kGemmThreads), 0, s, g);
+    hipLaunchKernelGGL((grouped_gemm_kernel<GATED, BM>), dim3((unsigned)blocks), dim3(kGemmThreads), 0, s, g);
     return hipGetLastError();
 }
 
-// ---- bf16 grouped GEMM with direct global->LDS loads (K % BK == 0)
-//
-// 256 x 256 workgroup tile (gate/up: 128 columns of each matrix), 128 x 128
-// per wave, a ring of LDS stages filled by global_load_lds_dwordx4 (no
-// staging registers, no LDS store instructions). A stage holds every tile
-// row's BK k-values as one LDS row of BK*2 bytes whose 16-byte chunks are
-// XOR-swizzled by (row >> 1), so the 32 rows of an MFMA fragment read without
-// bank conflicts; one DMA instruction fills 64/(BK/8) consecutive rows, each
-// lane fetching the global chunk that belongs in its LDS slot (the lanes of a
-// row read the row's contiguous bytes). The DMA and the barrier are issued
-// through inline asm: with the builtin, the compiler would wait for every
-// outstanding DMA before each LDS read and at each barrier, defeating the ring.
-// Per K-step (four MFMA sub-steps of k = 16): by the end of sub-step 0
-// every fragment of the stage is in registers (sub-steps 0 and 1 were read
-// during the previous K-step), and a barrier releases its slot; sub-steps
-// 1-3 issue the copies of K-step kt+2 into it (6, 5 and 5 per wave); after
-// sub-step 2 a wait for this wave's older copies and a second barrier make
-// K-step kt+1 resident, and sub-step 3 reads its first two sub-steps.
-
-// K-step and ring depth of the DMA kernels. BK = 64 makes every DMA row a
-// full 128-byte line (8 rows per instruction), which the L2 and MALL serve
-// faster than 64-byte pieces; two 64 KB stages leave one stage in flight.
-// Measured on the grouped workloads, more stages of BK = 32 did not help:
-// the pipeline is bound by L2/MALL throughput, not by latency.
-// ---- bf16 grouped GEMM with direct-to-LDS copies (large groups)
+// ---- bf16 grouped GEMM with direct-to-LDS copies
 //
 // 256x256 workgroup tile (gate/up: 128 columns of each of W_gate and W_up, so
-// SiLU(gate)*up happens in the epilogue), 128x128 per wave, 32x32x16 bf16 MFMA
-// with fp32 accumulators, K-step 64 through a two-slot LDS ring filled by
-// global_load_lds_dwordx4.
+// SiLU(gate)*up happens in the epilogue) or half its height, 128x128 (64x128)
+// per wave, 32x32x16 bf16 MFMA with fp32 accumulators, K-steps of 64 through a
+// ring of two LDS stages filled by global_load_lds_dwordx4 (no staging
+// registers, no LDS store instructions). A stage holds every tile row's BK
+// k-values as one LDS row of BK*2 bytes whose 16-byte chunks are XOR-swizzled
+// by (row >> 1), so the 32 rows of an MFMA fragment read without bank
+// conflicts; one DMA instruction fills 64/(BK/8) consecutive rows, each lane
+// fetching the global chunk that belongs in its LDS slot (the lanes of a row
+// read the row's contiguous bytes). The DMA and the barrier are issued through
+// inline asm: with the builtin, the compiler would wait for every outstanding
+// DMA before each LDS read and at each barrier, defeating the ring.
+// Per K-step (four MFMA sub-steps of k = 16): by the end of sub-step 0 every
+// fragment of the stage is in registers (sub-steps 0 and 1 were read during the
+// previous K-step), and a barrier releases its slot; sub-steps 1-3 issue the
+// copies of K-step kt+2 into it (6, 5 and 5 per wave; 4, 4 and 4 for a half
+// tile); after sub-step 2 a wait for this wave's older copies and a second
+// barrier make K-step kt+1 resident, and sub-step 3 reads its first two
+// sub-steps. BK = 64 makes every DMA row a full 128-byte line (8 rows per
+// instruction), which the L2 and MALL serve faster than 64-byte pieces; more
+// stages of BK = 32 did not help: the pipeline is bound by L2/MALL throughput,
+// not by latency. K that is not whole K-steps: tail_cols, below.
 //
 // Work distribution: one workgroup per CU, rounds of one tile per workgroup.
 // With a workspace (stream-K) the K-steps of the last tiles may be split evenly
-// across the workgroups instead. A workgroup
-// whose share starts or ends inside a tile writes that piece's fp32
-// accumulators to its workspace slot, and a second kernel sums the pieces of
-// each split tile in K order and applies the epilogue. No workgroup ever
-// waits for another, so nothing depends on which workgroups are resident.
+// across the workgroups instead. A workgroup whose share starts or ends inside a
+// tile writes that piece's fp32 accumulators to its workspace slot, and a second
+// kernel sums the pieces of each split tile in K order and applies the epilogue.
+// No workgroup ever waits for another, so nothing depends on which workgroups
+// are resident.
 
 constexpr int kGroupM = 8;
 constexpr int kDmaBK = 64;
@@ -796,19 +793,13 @@ __device__ __forceinline__ void tile_ksteps(f32x16 (&acc)[C::NMAT][C::MB][C::NB]
     else wait_vmcnt<0>();
     wg_barrier();
     // Fragments two sub-steps ahead, in four register sets (set j holds
-    // sub-step j of a K-step). Sub-step j reads sub-step j+2 (the next
-    // K-step's slot for j >= 2). After sub-step 1 every fragment of this
-    // K-step's slot is in registers: one barrier then releases the slot and
-    // (after this wave's wait) makes the next K-step's slot resident, and
-    // sub-steps 2 and 3 issue the copies of K-step kt+2 into the released
-    // slot, one per two MFMAs.
+    // sub-step j of a K-step). Sub-step 0 reads sub-steps 2 and 3, so a barrier
+    // after it releases the slot; sub-steps 1-3 issue the copies of K-step kt+2
+    // into it; after sub-step 2 a wait for this wave's older copies and a second
+    // barrier make K-step kt+1 resident; sub-step 3 reads its sub-steps 0 and 1.
     static_assert(C::SUB == 4, "four sub-steps per K-step");
     uint4 af[4][C::MB];
     uint4 bf[4][C::NMAT][C::NB];
-    // Sub-step 0 reads sub-steps 2 and 3, so a barrier after it releases the
-    // slot; sub-steps 1-3 issue the copies of K-step kt+2 (6, 5, 5); after
-    // sub-step 2 a wait for this wave's older copies and a second barrier
-    // make K-step kt+1 resident; sub-step 3 reads its sub-steps 0 and 1.
     dma_frags<C, MB>(af[0], bf[0], smem + (s0 & 1) * C::STAGE, wm, wn, lane, 0);
     dma_frags<C, MB>(af[1], bf[1], smem + (s0 & 1) * C::STAGE, wm, wn, lane, 1);
     const int tv = tail_cols<C>(p);
@@ -1281,7 +1272,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_fixup_kernel(GemmParams p, 
         }
 #pragma unroll
         for (int k = 0; k < QPER; ++k) {
-            const int qq = qs * QPER + k;  // slot (mb, nb, i4) in the order of store_piece
+            const int qq = qs * QPER + k;  // slot (mb, nb, i4) in the order of store_tile's pieces
             const int i4 = qq & 3, nb = (qq >> 2) % C::NB, mb = (qq >> 2) / C::NB;
             const int r0 = dma_arow(wm, mb, C::MB) + 8 * i4 + 4 * (lane >> 5);  // (split tiles are whole)
             const int gn = tc.n0 + wn * C::WTN + nb * 32 + (lane & 31);
@@ -1314,11 +1305,19 @@ static int stream_k_workgroups() {
 
 // Whether the kernel with half tiles and ragged K-steps (VAR) runs. Ragged K
 // needs it. Otherwise it saves the padding of the segments' last tiles, half a
-// tile in two on average, so 128 of rows_cap / n_seg rows, and costs 2-3 % of
-// the GEMMs in per-tile scalar work. With 400 rows per segment on average
-// (partial brownout, 3001 tokens) the layer runs 307-313 -> 285 us; with
-// 1024 rows and no tails 559 -> 564 us (grouping search), with 2184 rows
-// (fine-shaped) it gains at most 1 %, with 6144 (heavy-shaped) it loses 1 %.
+// tile in two on average, so 128 of rows_cap / n_seg rows, and costs 1-3 % in
+// per-tile scalar work; what it saves shows where it takes a round of workgroups
+// less. Both GEMMs on segments of random sizes, us, plain / VAR, by the rows per
+// segment on average:
+//   15 segments, d = 2048, d_ff = 1408: 300 139 / 116; 450 175 / 150; 600 185 /
+//     188; 768 228 / 224; 900 239 / 241; 1100 311 / 282; 1400 334 / 338; 2184 513 /
+//     517; 4500 1020 / 1032
+//   16 segments, d_ff = 2816: 300 229 / 216; 600 384 / 357; 768 416 / 426; 900 509
+//     / 482; 1400 700 / 687; 2184 1051 / 1061
+//   4 segments, d = 4096, d_ff = 14336: 150 371 / 360; 450 794 / 775; 600 932 /
+//     944; 768 988 / 994; 2184 2418 / 2442; 4500 4824 / 4843
+//   60 segments, d_ff = 1408: 150 289 / 274; 300 418 / 390; 600 668 / 649; 900 913
+//     / 903
 constexpr int kVarRows = 768;
 static bool gemm_var_pays(const GemmParams& g) {
     return g.K % kDmaBK != 0 || (int64_t)g.rows_cap < (int64_t)g.n_seg * kVarRows;
@@ -1399,7 +1398,7 @@ static bool gemm_dma_fits(const GemmParams& g) {
     if (g.K % kDmaBK == 0) return true;
     if (g.K <= 2 * kDmaBK) return false;
     const int64_t cus = persistent_workgroups(), rows = g.rows_cap, n = g.n_seg;
-    const int64_t tiles = (ceil_div64(rows, 128) + n) * ceil_div(g.N, GATED ? 128 : 256);  // register-staged, at most
+    const int64_t tiles = (ceil_div64(rows, 128) + n) * ceil_div(g.N, GemmCfg<GATED, 128>::BN);  // register-staged, at most
     if (tiles > cus) return true;
     const bool tall = rows >= 96 * n;  // groups past a half tile on average, nearly
     const bool staged = GATED ? tall && g.K < 448 && g.K * tiles <= 300 * cus
@@ -1423,14 +1422,14 @@ bool ffn_can_fold(const FfnArgs& a) {
 // round that the real rows just miss costs more, 8000 rows of d_ff = 1024 40 / 47.)
 template <bool GATED>
 static hipError_t launch_gemm_staged(const GemmParams& g, hipStream_t s) {
-    constexpr int BN = GATED ? 128 : 256;
+    constexpr int BN = GemmCfg<GATED, 128>::BN;
     if (g.K <= 2 * kDmaBK && (int64_t)g.rows_cap >= (int64_t)1024 * g.n_seg) {
         const int64_t cus = persistent_workgroups(), nt = ceil_div(g.N, BN);
         auto rounds = [&](int bm) { return ceil_div64((ceil_div64(g.rows_cap, bm) + g.n_seg / 2) * nt, cus); };
         if (GATED ? 4 * rounds(256) <= 3 * rounds(128) : 7 * rounds(256) <= 4 * rounds(128))
-            return launch_gemm<GATED, 256, BN, 64, kFdb256>(g, s);
+            return launch_gemm<GATED, 256>(g, s);
     }
-    return launch_gemm<GATED, 128, BN, 64, true>(g, s);
+    return launch_gemm<GATED, 128>(g, s);
 }
 
 hipError_t launch_ffn(const FfnArgs& a, hipStream_t s, int part) {

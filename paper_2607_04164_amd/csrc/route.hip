@@ -54,10 +54,8 @@ static_assert(BMOE_MAX_EXPERTS <= kRouteThreads, "one map entry per thread");
 enum { MODE_LOGITS_IN = 0, MODE_F32 = 1, MODE_BF16 = 2, MODE_BF16_RES = 3, MODE_BF16_XD = 4, MODE_BF16_WR = 5 };
 __host__ __device__ constexpr bool mode_bf16(int mode) { return mode >= MODE_BF16; }
 
-// KW of MODE_BF16_XD carries NU (k-steps of 32 columns per wave, low 6 bits)
-// and NS (ring slots, the bits above)
-__host__ __device__ constexpr int xd_nu(int kw) { return kw & 63; }
-__host__ __device__ constexpr int xd_ns(int kw) { return kw >> 6; }
+// KW of MODE_BF16_XD is NU (k-steps of 32 columns per wave)
+constexpr int kXdNS = 3;                  // ring slots
 constexpr int kXdSlot = 16 * 1024;        // 64 router rows x 2 column halves x 64 columns, bf16
 constexpr int kXdPart = 2 * 16 * 64 * 4;  // partial tiles of the waves of the second half
 
@@ -116,7 +114,7 @@ __host__ __device__ inline RouteSmem route_smem(int E, int d) {
     if constexpr (MODE == MODE_F32) s.ring_bytes = kResPartBytes;
     if constexpr (MODE == MODE_BF16_RES) s.ring_bytes = res_w_bytes(d) + kResPartBytes;
     if constexpr (MODE == MODE_BF16_WR) s.ring_bytes = (size_t)4 * KW * wr_slot(TB, NBLK);
-    if constexpr (MODE == MODE_BF16_XD) s.ring_bytes = (size_t)xd_ns(KW) * kXdSlot + kXdPart;
+    if constexpr (MODE == MODE_BF16_XD) s.ring_bytes = (size_t)kXdNS * kXdSlot + kXdPart;
     return s;
 }
 
@@ -705,11 +703,11 @@ __device__ __forceinline__ void logits_bf16_res(const RouteArgs& p, float* zs, c
 // for the whole x tile before the ring loop (a wait for one x load inside it
 // would also wait for every copy issued after that load). The halves' partial
 // tiles are summed in a fixed order.
-template <int NU, int NS>
+template <int NU>
 __device__ __forceinline__ void logits_bf16_xd(const RouteArgs& p, float* zs, char* ring, char* dummy, float* part,
                                                int t0) {
+    constexpr int NS = kXdNS;
     constexpr int NSTEP = NU / 2;  // 64 columns of each half per ring step
-    static_assert(NSTEP >= 1 && NS >= 2 && NS <= 8, "ring shape");
     const uint16_t* x = (const uint16_t*)p.x;
     const uint16_t* w = (const uint16_t*)p.w;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -993,7 +991,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs p) {
     } else if constexpr (MODE == MODE_BF16_WR) {
         logits_bf16_wr<TB, NBLK, KW>(p, zs, ring, t0);
     } else if constexpr (MODE == MODE_BF16_XD) {
-        logits_bf16_xd<xd_nu(KW), xd_ns(KW)>(p, zs, ring, dummy, (float*)(ring + xd_ns(KW) * kXdSlot), t0);
+        logits_bf16_xd<KW>(p, zs, ring, dummy, (float*)(ring + kXdNS * kXdSlot), t0);
     } else if constexpr (MODE == MODE_F32) {
         logits_f32(p, zs, sm.zstride, (float*)ring, t0);
     } else {
@@ -1262,14 +1260,10 @@ hipError_t launch_res(const RouteArgs& a, hipStream_t s) {
 bool xd_fits(const RouteArgs& a) {
     return a.E > 16 && a.E <= 64 && (a.d == 512 || a.d == 1024 || a.d == 2048);
 }
-template <int NU>
-hipError_t launch_xd_nu(const RouteArgs& a, hipStream_t s) {
-    return launch_one<MODE_BF16_XD, 2, 4, NU + 64 * 3>(a, s);
-}
 hipError_t launch_xd(const RouteArgs& a, hipStream_t s) {
-    if (a.d == 2048) return launch_xd_nu<32>(a, s);
-    if (a.d == 1024) return launch_xd_nu<16>(a, s);
-    return launch_xd_nu<8>(a, s);
+    if (a.d == 2048) return launch_one<MODE_BF16_XD, 2, 4, 32>(a, s);
+    if (a.d == 1024) return launch_one<MODE_BF16_XD, 2, 4, 16>(a, s);
+    return launch_one<MODE_BF16_XD, 2, 4, 8>(a, s);
 }
 
 // x and W_router through rings of the waves' own: up to 64 experts, d of whole
