@@ -1318,6 +1318,9 @@ static int stream_k_workgroups() {
 //     944; 768 988 / 994; 2184 2418 / 2442; 4500 4824 / 4843
 //   60 segments, d_ff = 1408: 150 289 / 274; 300 418 / 390; 600 668 / 649; 900 913
 //     / 903
+// (Where all tiles are one round either way, 80 to 350 rows, single GEMMs are 7 %
+// faster to 9 % slower with no rule in sizes: 8 segments, 250 rows, gate/up 49 / 55,
+// 4 segments, d_ff = 14336, 300 rows, down 320 / 299.)
 constexpr int kVarRows = 768;
 static bool gemm_var_pays(const GemmParams& g) {
     return g.K % kDmaBK != 0 || (int64_t)g.rows_cap < (int64_t)g.n_seg * kVarRows;
