@@ -386,10 +386,11 @@ __global__ __launch_bounds__(kSkThreads, 1) void skinny_dma_kernel(SkinnyParams 
 // registers in the MFMA layout. Bound by the latency of the loads, so PAIRS
 // pairs per wave are in flight at once, with the activations of the first 16
 // rows; further row tiles reuse the weights. The partial tiles are added
-// through LDS in wave order. Weights cold, d = 2048, d_ff = 1408, top-4, in us,
-// ring -> this kernel: 1 token gate/up 15.5 -> 12.4, down 9.0 -> 8.0; 12 tokens
-// (15 groups) 39.4 -> 32.2, 17.0 -> 14.5; d_ff = 176, 4 tokens 15.1 -> 7.4,
-// 9.3 -> 3.9.
+// through LDS in wave order. Ring -> this kernel, in us, d = 2048, d_ff = 1408,
+// 15 groups, weights cold, means of 10 routing draws: one token of top-4 gate/up
+// 16.3 -> 13.5, down 9.7 -> 8.4 (in the layer, weights in the last-level cache, by
+// the kernel trace 17.4 -> 15.8 and 8.8 -> 7.4); 24 tokens 39.0 -> 32.5 and 17.9 ->
+// 16.3; d_ff = 176, 4 tokens 15.1 -> 7.6 and 9.4 -> 4.0.
 constexpr int kRgCols = 16;  // output columns per workgroup
 
 // Pairs in flight per wave: gate/up the eight that 256 registers hold (all of
