@@ -529,7 +529,8 @@ __global__ __launch_bounds__(kSkThreads, 2) void skinny_reg_kernel(SkinnyParams 
 // means of 10 routing draws, d = 2048 and d_ff = 1408 where not given.
 //  gate/up:
 //  - under 0.45 of the CUs busy: 4 rows, 15 segments 16.3 / 13.5; 8 rows 17.0 /
-//    16.4; d_ff = 704, 24 rows 17.2 / 14.9; d = 4096, d_ff = 3584, 2 rows 29.5 /
+//    16.4; d_ff = 704, 24 rows 17.2 / 14.9; d_ff = 352, 80 rows 0.94, 120 rows 1.08
+//    of the ring kernel's time; d = 4096, d_ff = 3584, 2 rows 29.5 /
 //    24.8; one segment (a shared expert), d_ff = 2816, 1 to 16 rows 0.54-0.60 of
 //    the ring kernel's time. Above, the ring kernel is already near the stream
 //    rate: 60 segments, 8 rows 17.8 / 19.3; d = 4096, d_ff = 1792, 12 rows 31.9 /
@@ -538,7 +539,10 @@ __global__ __launch_bounds__(kSkThreads, 2) void skinny_reg_kernel(SkinnyParams 
 //    competes with the slower register-staged kernel;
 //  - the ring kernel's second round of workgroups, up to half full: 15
 //    segments, 64 rows 31.7 / 29.9, 96 rows 39.0 / 32.5; d = 4096, d_ff = 3584,
-//    16 rows 74.7 / 68.1, 48 rows (the line) 87-93 / 88, but 96 rows 90.4 / 98.2;
+//    16 rows 74.7 / 68.1, 48 rows (the upper line) 87-93 / 88, but 96 rows 90.4 /
+//    98.2. At the lower line it depends on the routing: 15 segments, 48 rows, top-4
+//    of 60 26.0 / 28.0 (single draws to 38.8 / 32.1), top-6 of 64 33.1 / 30.2; 40 rows
+//    24.1 / 26.0;
 //  - so few columns that the ring kernel never fills a quarter of the CUs: d_ff =
 //    176, 16 rows 15.2 / 8.4, 240 rows 15.4 / 13.5.
 //  down:
@@ -572,8 +576,8 @@ bool takes_reg(const SkinnyParams& p) {
         // (from two rows per segment on, as if all of them had rows)
         const double few = rows < 2 * n ? 0.45 : (double)most <= 0.5 * cus ? 0.45 : 0.0;
         const bool long_k = p.K >= 512 || p.K % kS2KC;
-        return (long_k && rows <= (n > 6 ? 8 * n : 48) && busy <= few * cus) ||
-               (busy > cus && busy <= 1.5 * cus && (double)most <= 2.0 * cus);
+        return (long_k && rows <= (n > 6 ? 6 * n : 48) && busy <= few * cus) ||
+               (busy > 0.97 * cus && busy <= 1.5 * cus && (double)most <= 2.0 * cus);
     }
     if (p.K % kS2KC && p.K <= 512) return true;
     const bool in_flight = p.K <= 6 * 4 * 64;  // all of K (launch_skinny)

@@ -33,7 +33,8 @@ SKINNY = [
     ("up", 15, 4, 2048, 1408, REG), ("up", 15, 8, 2048, 1408, REG), ("up", 60, 8, 2048, 1408, RING),
     ("up", 64, 6, 2048, 1408, RING), ("up", 8, 6, 4096, 1792, REG), ("up", 8, 12, 4096, 1792, RING),
     ("up", 60, 48, 2048, 352, REG), ("up", 60, 128, 2048, 352, RING), ("up", 15, 240, 2048, 176, REG),
-    ("up", 15, 48, 2048, 1408, RING), ("up", 15, 96, 2048, 1408, REG), ("up", 15, 160, 2048, 1408, RING),
+    ("up", 15, 80, 2048, 352, REG), ("up", 15, 120, 2048, 352, RING),
+    ("up", 15, 40, 2048, 1408, RING), ("up", 15, 48, 2048, 1408, REG), ("up", 15, 96, 2048, 1408, REG), ("up", 15, 160, 2048, 1408, RING),
     ("up", 8, 16, 4096, 3584, REG), ("up", 8, 48, 4096, 3584, REG), ("up", 8, 96, 4096, 3584, RING),
     ("up", 1, 16, 2048, 2816, REG), ("down", 1, 16, 2048, 2816, REG), ("down", 2, 32, 2048, 2816, REG),
     ("down", 15, 4, 2048, 1408, REG), ("down", 60, 96, 2048, 1408, REG), ("down", 60, 128, 2048, 1408, RING),
