@@ -765,6 +765,10 @@ __device__ __forceinline__ void logits_bf16_xd(const RouteArgs& p, float* zs, ch
     for (int c = 0; c < NSTEP; ++c) {
         // copies issued so far: steps 0 .. min(NSTEP - 1, c + NS - 2)
         wait_vmcnt_rt<4>(min(NSTEP - 1 - c, NS - 2));
+        // this wave's reads of the previous step's slot too (the compiler sinks
+        // their waits past the barrier): the next copies, which hit in L1 when
+        // the CU's other workgroup is ahead, could overtake them
+        lds_reads_done();
         wg_barrier();
         // the slot read in the previous step is free for step c + NS - 1
         if (c + NS - 1 < NSTEP) issue(c + NS - 1, (c + NS - 1) % NS);

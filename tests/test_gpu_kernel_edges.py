@@ -269,3 +269,31 @@ def test_route_paths(E, d, k, T):
         assert np.array_equal(got[key].cpu().numpy(), ref[key]), key
     assert_gates(got["topk_w"].cpu().numpy(), ref["topk_w"], "topk_w")
     assert_gates(got["slot_gate"].cpu().numpy(), ref["slot_gate"], "slot_gate")
+
+
+@pytest.mark.parametrize("E,d,T", [(64, 2048, 16384), (33, 1024, 9000), (60, 512, 12289)])
+def test_route_two_workgroups_per_cu_repeats(E, d, T):
+    """x straight into registers, two workgroups per CU: the same bits on every
+    call, alone and beside copies on another stream, and logits within a quarter
+    of the gap of their float64 values."""
+    gen = torch.Generator(device="cuda").manual_seed(E)
+    x = torch.randn(T, d, generator=gen, device="cuda").bfloat16()
+    w = (torch.randn(E, d, generator=gen, device="cuda") / d ** 0.5).bfloat16()
+    e2g = (torch.arange(E, device="cuda", dtype=torch.int32) % 16).contiguous()
+    desc = B.make_desc(T, d, E, 6, 16, 64)
+    first = B.route(desc, x, w, None, e2g, want_logits=True)
+    z = x.double() @ w.double().t()
+    assert float((first["logits"].double() - z).abs().max()) < B.ROUTE_RECHECK_GAP / 4
+    side, a, b = torch.cuda.Stream(), torch.empty(64 << 20, dtype=torch.uint8, device="cuda"), None
+    side.wait_stream(torch.cuda.current_stream())
+    runs = []
+    for i in range(12):
+        if i >= 6:
+            with torch.cuda.stream(side):
+                b = a.clone()
+        runs.append(B.route(desc, x, w, None, e2g, want_logits=True))
+    torch.cuda.synchronize()
+    for i, r in enumerate(runs):
+        for k, v in first.items():
+            assert torch.equal(r[k], v), (i, k)
+    del b
